@@ -70,20 +70,22 @@ typedef struct mer_view {
   int32_t n_v, n_t, H, W;
 } mer_view;       /* 48 bytes, no padding */
 
-/* Tile shape (pixels), bin pool capacity (triangle-tile entries, at most
- * INT_MAX - 1; 0 picks a default from the triangle and tile counts; tiles
- * whose entries do not fit are rasterized by a slower path that scans every
- * triangle of their view) and the small-triangle limit:
- * a triangle whose box of pixel centres holds at most small_px centres is
- * rasterized by its set-up thread directly into the per-pixel z-buffer key
- * instead of being binned (0 picks the default 16, a negative value bins
- * every triangle).  The results do not depend on any of these. */
+/* How triangles are binned.  By default (small_px >= 0) each triangle is
+ * listed in the coarse screen tiles it may cover, 8, 16 or 32 pixels square
+ * (mer_plan_init picks the side from the view sizes and the triangle count),
+ * and the tile's workgroup sorts them into 8x8 pixels itself; tile_w, tile_h
+ * and big_tiles have no effect.  With small_px < 0 every triangle is listed in
+ * the tile_w x tile_h tiles it may cover and the rasterizer takes one such
+ * tile per workgroup.  bin_cap is the capacity of the list pool (entries, at
+ * most INT_MAX - 1; 0 picks a default from the triangle and tile counts);
+ * tiles whose entries do not fit are rasterized by a slower path that scans
+ * every triangle of their view.  The results do not depend on any of these. */
 typedef struct mer_tuning {
   int32_t tile_w, tile_h; /* supported: 8x8, 16x16, 32x8, 16x8 */
   int64_t bin_cap;
-  int32_t small_px;
-  int32_t big_tiles; /* a triangle whose box spans more tiles is binned by a
-                        whole wave (0: default 16; negative: never) */
+  int32_t small_px;  /* negative: lists of tile_w x tile_h tiles (above) */
+  int32_t big_tiles; /* with those: a triangle whose box spans more tiles is
+                        binned by a whole wave (0: default 16; negative: never) */
 } mer_tuning;
 
 /* Host-side plan: totals over the view table and the workspace layout.
@@ -102,6 +104,8 @@ typedef struct mer_plan {
   int64_t big_tiles;                  /* see mer_tuning */
   int64_t n_bingroups, off_bigflat;   /* workgroups of the binning passes; the packed list */
   int64_t off_bigpart;                /* scan partials of the list lengths */
+  int64_t ct_log2, total_ctiles;      /* coarse tiles: log2 of their side, their number */
+  int64_t off_ccount, off_ctile;      /* coarse tile counters; their lists and places */
 } mer_plan;
 
 /* One pinhole camera per view for the vertex transform: the rows of R are

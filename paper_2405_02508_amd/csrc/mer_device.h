@@ -15,6 +15,30 @@ namespace mer {
 constexpr float kGuard = 1048576.0f;  // |x|,|y| beyond 2^20 px -> culled
 constexpr float kZNear = 1.0e-3f;     // z at or below -> culled
 
+// RN(1 / x) for normal x > 0: the hardware reciprocal (within 1 ulp) and one
+// Newton step with an exact remainder.  Compared with the IEEE quotient on
+// every binary32 value in [2^-120, 2^120] on gfx950: no difference.  Three
+// operations in place of the division's ten; outside that range (a result
+// near the denormals) the division itself.
+__device__ __forceinline__ float rcp_step(float x) {
+  const float y = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, y, 1.0f), y, y);
+}
+__device__ __forceinline__ float rcp_rn(float x) {
+  float r = rcp_step(x);
+  if (__builtin_expect(!(x >= 0x1p-120f && x <= 0x1p120f), 0)) r = 1.0f / x;
+  return r;
+}
+// The same of three vertex depths (each at least 1e-3): one branch for all.
+__device__ __forceinline__ void rcp_rn3(const float z[3], float q[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) q[k] = rcp_step(z[k]);
+  if (__builtin_expect(!(fmaxf(z[0], fmaxf(z[1], z[2])) <= 0x1p120f), 0)) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q[k] = 1.0f / z[k];
+  }
+}
+
 // Per (view, triangle) set-up record, 64 bytes.  For edge k (opposite vertex
 // k) and pixel (px, py):  E'_k = A[k] * (256 px) + B[k] * (256 py) + C[k]
 // equals sign(D) * orient(v_{k+1}, v_{k+2}, centre) + tl_k, so the centre is
@@ -78,12 +102,40 @@ __device__ __forceinline__ Snap snap_triangle(const float* __restrict__ v, const
     const float x = ok ? p[3 * k] : 0.f, y = ok ? p[3 * k + 1] : 0.f, z = ok ? p[3 * k + 2] : 1.f;
     s.X[k] = (int)rintf(x * 256.0f);
     s.Y[k] = (int)rintf(y * 256.0f);
-    s.q[k] = ok ? (EXACT_Q ? 1.0f / z : __builtin_amdgcn_rcpf(z)) : 0.f;
-    s.z[k] = ok ? z : 0.f;
+    s.z[k] = z;
+    if (!EXACT_Q) s.q[k] = __builtin_amdgcn_rcpf(z);
+  }
+  if (EXACT_Q) rcp_rn3(s.z, s.q);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    s.q[k] = ok ? s.q[k] : 0.f;
+    s.z[k] = ok ? s.z[k] : 0.f;
   }
   s.D = (long long)(s.X[1] - s.X[0]) * (long long)(s.Y[2] - s.Y[0]) -
         (long long)(s.X[2] - s.X[0]) * (long long)(s.Y[1] - s.Y[0]);
   s.ok = ok && s.D != 0;
+  return s;
+}
+
+// snap_triangle of a triangle known to pass its checks (one that is visible
+// somewhere in this rasterization), same values.
+__device__ __forceinline__ Snap snap_visible(const float* __restrict__ v, const mer_view& vw,
+                                             const int32_t* __restrict__ row) {
+  Snap s;
+  const float* vb = v + vw.v_off * 3;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) s.idx[k] = row[k];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float* q = vb + (size_t)(unsigned)s.idx[k] * 3u;
+    s.X[k] = (int)rintf(q[0] * 256.0f);
+    s.Y[k] = (int)rintf(q[1] * 256.0f);
+    s.z[k] = q[2];
+  }
+  rcp_rn3(s.z, s.q);
+  s.D = (long long)(s.X[1] - s.X[0]) * (long long)(s.Y[2] - s.Y[0]) -
+        (long long)(s.X[2] - s.X[0]) * (long long)(s.Y[1] - s.Y[0]);
+  s.ok = true;
   return s;
 }
 
@@ -408,11 +460,37 @@ __device__ __forceinline__ PixBary pixel_bary(const Snap& s, int px, int py) {
 // perspective-correct barycentrics b0, b1 (beta_k q_k / W with |D| cancelled);
 // the rasterizer keeps these products for the winning candidate.
 __device__ __forceinline__ void resolve_products(const Snap& s, int px, int py, float& a, float& b, float& n) {
-  long long E[3];
-  edge_at(s, px, py, E);
-  a = (float)E[0] * s.q[0];
-  b = (float)E[1] * s.q[1];
-  const float c = (float)E[2] * s.q[2];
+  float e[3];
+  // With every vertex less than 2^15 (128 px) from the centre along each axis
+  // the edge values are differences of two products below 2^30: 32 bits hold
+  // them, and the 24-bit multiplier gives the products.
+  int x[3], y[3];
+  unsigned m = 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    x[k] = s.X[k] - (px * 256 + 128);
+    y[k] = s.Y[k] - (py * 256 + 128);
+    m |= ((unsigned)x[k] + (1u << 15)) | ((unsigned)y[k] + (1u << 15));
+  }
+  if (m < (1u << 16)) {
+    int E[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int i = (k + 1) % 3, j = (k + 2) % 3;
+      E[k] = mul_i24(x[i], y[j]) - mul_i24(x[j], y[i]);
+    }
+    const bool neg = s.D < 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) e[k] = (float)(neg ? -E[k] : E[k]);
+  } else {
+    long long E[3];
+    edge_at(s, px, py, E);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) e[k] = (float)E[k];
+  }
+  a = e[0] * s.q[0];
+  b = e[1] * s.q[1];
+  const float c = e[2] * s.q[2];
   n = a + b;
   n = n + c;
 }
@@ -477,6 +555,46 @@ __device__ __forceinline__ void grid_xy(long long local, int w, int& x, int& y) 
   x = (int)(l - q * uw);
 }
 
+// Per-view prefixes of triangles and of 2^tw_log2 x 2^th_log2 tiles, by one
+// workgroup of 1024 threads (any number of views); status[0..8) = 0 unless NULL.
+__device__ __forceinline__ void view_prefix(const mer_view* __restrict__ views, int n_views, int tw_log2, int th_log2,
+                                            long long* __restrict__ tri_base, long long* __restrict__ tile_base,
+                                            long long* __restrict__ status) {
+  __shared__ long long s_tri[1024], s_tile[1024];
+  const int tid = threadIdx.x;
+  const int per = (n_views + 1023) / 1024;
+  const int lo = tid * per, hi = min(n_views, lo + per);
+  long long a = 0, b = 0;
+  for (int i = lo; i < hi; ++i) {
+    const mer_view vw = views[i];
+    a += vw.n_t;
+    b += (long long)((vw.W + (1 << tw_log2) - 1) >> tw_log2) * ((vw.H + (1 << th_log2) - 1) >> th_log2);
+  }
+  s_tri[tid] = a;
+  s_tile[tid] = b;
+  __syncthreads();
+  for (int off = 1; off < 1024; off <<= 1) {
+    long long x = tid >= off ? s_tri[tid - off] : 0, y = tid >= off ? s_tile[tid - off] : 0;
+    __syncthreads();
+    s_tri[tid] += x;
+    s_tile[tid] += y;
+    __syncthreads();
+  }
+  long long ea = s_tri[tid] - a, eb = s_tile[tid] - b;  // exclusive prefix of this thread's chunk
+  for (int i = lo; i < hi; ++i) {
+    const mer_view vw = views[i];
+    tri_base[i] = ea;
+    tile_base[i] = eb;
+    ea += vw.n_t;
+    eb += (long long)((vw.W + (1 << tw_log2) - 1) >> tw_log2) * ((vw.H + (1 << th_log2) - 1) >> th_log2);
+  }
+  if (tid == 1023) {
+    tri_base[n_views] = s_tri[1023];
+    tile_base[n_views] = s_tile[1023];
+  }
+  if (status && tid < 8) status[tid] = 0;
+}
+
 // Largest i in [0, n) with base[i] <= g (base non-decreasing, base[0] <= g).
 template <typename T>
 __device__ __forceinline__ int find_bucket(const T* base, int n, long long g) {
@@ -517,6 +635,60 @@ __device__ __forceinline__ int wave_view(const mer_view* views, int n, long long
   const long long u = ((long long)__builtin_amdgcn_readfirstlane((int)(p0 >> 32)) << 32) |
                       (unsigned)__builtin_amdgcn_readfirstlane((int)(p0 & 0xffffffff));
   return __builtin_amdgcn_readfirstlane(find_view_px(views, n, u));
+}
+
+// Wave reductions and scans through DPP row shifts and row broadcasts (no LDS
+// round trips).  A lane without a source takes the operation's identity.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_min(unsigned x) {
+  return min(x, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)x, CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_zero(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ unsigned wave_min_u32(unsigned x) {
+  x = dpp_min<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8
+  x = dpp_min<0x112, 0xf>(x);
+  x = dpp_min<0x114, 0xf>(x);
+  x = dpp_min<0x118, 0xf>(x);
+  x = dpp_min<0x142, 0xa>(x);  // row_bcast:15, 31
+  x = dpp_min<0x143, 0xc>(x);
+  return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+__device__ __forceinline__ unsigned wave_max_u32(unsigned x) { return ~wave_min_u32(~x); }
+// inclusive sum over the lanes of a wave
+__device__ __forceinline__ int wave_scan_i32(int x) {
+  x += dpp_zero<0x111, 0xf>(x);
+  x += dpp_zero<0x112, 0xf>(x);
+  x += dpp_zero<0x114, 0xf>(x);
+  x += dpp_zero<0x118, 0xf>(x);
+  x += dpp_zero<0x142, 0xa>(x);
+  x += dpp_zero<0x143, 0xc>(x);
+  return x;
+}
+
+__device__ __forceinline__ long long wave_incl_scan(long long x) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  return x;
+}
+
+// RN(a / b) from y = RN(1 / b), for a >= 0 and b >= 1 with every step a
+// normal number: q0 = RN(a y) is within 1.5 ulp of a / b, one correction
+// with the remainder (exact product in the fma) brings it within one ulp,
+// and then the remainder is exact and one more correction gives the
+// correctly rounded quotient (Markstein's theorem on division with a fused
+// multiply-add).  Five operations in place of the division's scale, fix-up
+// and reciprocal sequence; the result is the IEEE quotient bit for bit.
+__device__ __forceinline__ float div_rn(float a, float b, float y) {
+  const float q0 = a * y;
+  const float q1 = fmaf(fmaf(-b, q0, a), y, q0);
+  return fmaf(fmaf(-b, q1, a), y, q1);
 }
 
 }  // namespace mer

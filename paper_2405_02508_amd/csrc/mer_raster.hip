@@ -2,74 +2,36 @@
 // rasterizer with barycentric/depth resolve (supplement, "Rasterization
 // module" and "Barycentrics module").
 //
-// Pipeline for one mer_rasterize call over all views:
+// Plans bin into coarse tiles (mer_coarse.h) unless they ask for lists of
+// their own tile shape (small_px < 0), which this file builds:
 //   k_prep      per-view prefix tables (triangles, tiles), clear tile counters
-//   k_setup     one thread per (view, triangle): snap, cull; a triangle whose
-//               box of pixel centres is small is rasterized right there
-//               (coverage + depth key + 64-bit atomic max into the per-pixel
-//               key); a larger one gets a 64-byte coverage record, its box,
-//               and counts the tiles it overlaps
+//   k_setup     one thread per (view, triangle): snap, cull; a 64-byte coverage
+//               record, its box, and the count of the tiles it overlaps
 //   k_scan_*    exclusive scan of tile counts -> bin offsets
 //   k_fill      one thread per (view, triangle): write its record index into
 //               every overlapped tile's list
-//   k_raster    one workgroup per tile, one lane per pixel: start from the
-//               pixel's key, stage the tile's records in LDS, exact coverage,
-//               binary32 depth key, 64-bit (1/z, ~id) max; then resolve the
-//               winner's depth and barycentrics from its vertices
+//   k_raster    one workgroup per tile, one lane per pixel: stage the tile's
+//               records in LDS, exact coverage, binary32 depth key, 64-bit
+//               (1/z, ~id) max; then resolve the winner's depth and
+//               barycentrics from its vertices
 // The (1/z, ~id) maximum does not depend on the order in which candidates
-// arrive, so both paths and any tile shape give the same index image.
+// arrive, so any tile shape gives the same index image.
 #include "mer_internal.h"
+#include "mer_coarse.h"
+#include "mer_resolve.h"
 
 namespace mer {
 
 // ----------------------------------------------------------------- prep
-// Block-wide exclusive scan over n values (any n); one block of 1024 threads.
 __global__ void __launch_bounds__(1024) k_prep(const mer_view* __restrict__ views, int n_views, int tw_log2,
                                                int th_log2, long long* __restrict__ tri_base,
                                                long long* __restrict__ tile_base, long long* __restrict__ status) {
-  __shared__ long long s_tri[1024], s_tile[1024];
-  const int tid = threadIdx.x;
-  const int per = (n_views + 1023) / 1024;
-  const int lo = tid * per, hi = min(n_views, lo + per);
-  long long a = 0, b = 0;
-  for (int i = lo; i < hi; ++i) {
-    const mer_view vw = views[i];
-    a += vw.n_t;
-    b += (long long)((vw.W + (1 << tw_log2) - 1) >> tw_log2) * ((vw.H + (1 << th_log2) - 1) >> th_log2);
-  }
-  s_tri[tid] = a;
-  s_tile[tid] = b;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    long long x = tid >= off ? s_tri[tid - off] : 0, y = tid >= off ? s_tile[tid - off] : 0;
-    __syncthreads();
-    s_tri[tid] += x;
-    s_tile[tid] += y;
-    __syncthreads();
-  }
-  long long ea = s_tri[tid] - a, eb = s_tile[tid] - b;  // exclusive prefix of this thread's chunk
-  for (int i = lo; i < hi; ++i) {
-    const mer_view vw = views[i];
-    tri_base[i] = ea;
-    tile_base[i] = eb;
-    ea += vw.n_t;
-    eb += (long long)((vw.W + (1 << tw_log2) - 1) >> tw_log2) * ((vw.H + (1 << th_log2) - 1) >> th_log2);
-  }
-  if (tid == 1023) {
-    tri_base[n_views] = s_tri[1023];
-    tile_base[n_views] = s_tile[1023];
-  }
-  if (status && tid < 8) status[tid] = 0;
+  view_prefix(views, n_views, tw_log2, th_log2, tri_base, tile_base, status);
 }
 
 __global__ void k_zero_i32(int* __restrict__ p, long long n) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
     p[i] = 0;
-}
-
-__global__ void k_zero_u64(unsigned long long* __restrict__ p, long long n) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    p[i] = 0ull;
 }
 
 // ---------------------------------------------------------------- setup
@@ -194,10 +156,9 @@ __global__ void __launch_bounds__(kBinBlock) k_setup(const mer_view* __restrict_
                                                const float* __restrict__ v, const int32_t* __restrict__ tri,
                                                const long long* __restrict__ tri_base,
                                                const long long* __restrict__ tile_base, long long total_tris,
-                                               int tw_log2, int th_log2, int small_px, int big_tiles,
-                                               long long px_begin,
+                                               int tw_log2, int th_log2, int big_tiles,
                                                Rec* __restrict__ rec, BBox* __restrict__ bbox,
-                                               int* __restrict__ count, unsigned long long* __restrict__ key,
+                                               int* __restrict__ count,
                                                long long* __restrict__ status, int* __restrict__ big,
                                                int* __restrict__ big_n) {
   __shared__ int s_tkey[kBinSlots], s_tcnt[kBinSlots], s_nocc;
@@ -226,25 +187,7 @@ __global__ void __launch_bounds__(kBinBlock) k_setup(const mer_view* __restrict_
       pya = max(pya, 0);
       pxb = min(pxb, vw.W - 1);
       pyb = min(pyb, vw.H - 1);
-      if (pxa <= pxb && pya <= pyb && (pxb - pxa + 1) * (pyb - pya + 1) <= small_px) {
-        // small triangle: rasterize its few pixel centres here
-        unsigned long long* kv = key + (vw.px_off - px_begin);
-        const long long dx0 = (long long)R.A[0] * 256, dx1 = (long long)R.A[1] * 256, dx2 = (long long)R.A[2] * 256;
-        for (int y = pya; y <= pyb; ++y) {
-          long long E[3];
-          edge_eval(R, pxa, y, E);  // then step along the row: E += 256 A
-          for (int x = pxa; x <= pxb; ++x) {
-            if (covered(E)) {
-              float e[3], d;
-              edge_values(R, E, e, d);
-              atomicMax(kv + (long long)y * vw.W + x, vis_key(depth_key(R, e, d), (int)t));
-            }
-            E[0] += dx0;
-            E[1] += dx1;
-            E[2] += dx2;
-          }
-        }
-      } else if (pxa <= pxb && pya <= pyb) {
+      if (pxa <= pxb && pya <= pyb) {
         Rec Rm = R;
         bb.x0 = (short)pxa;
         bb.x1 = (short)pxb;
@@ -291,16 +234,6 @@ __global__ void __launch_bounds__(kBinBlock) k_setup(const mer_view* __restrict_
 // with offsets saturated at INT_MAX: the bin pool is smaller than that, so a
 // tile whose range does not fit takes the raster's overflow path.  Blocks of
 // 256 threads x 4 items.
-__device__ __forceinline__ long long wave_incl_scan(long long x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const long long y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  return x;
-}
-
 __device__ __forceinline__ long long block_excl_scan_256(long long x, long long* s_wave, long long& total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const long long inc = wave_incl_scan(x);
@@ -504,19 +437,6 @@ struct __align__(16) TileRec {
 };
 static_assert(sizeof(TileRec) == 80, "tile record layout");
 
-// RN(a / b) from y = RN(1 / b), for a >= 0 and b >= 1 with every step a
-// normal number: q0 = RN(a y) is within 1.5 ulp of a / b, one correction
-// with the remainder (exact product in the fma) brings it within one ulp,
-// and then the remainder is exact and one more correction gives the
-// correctly rounded quotient (Markstein's theorem on division with a fused
-// multiply-add).  Five operations in place of the division's scale, fix-up
-// and reciprocal sequence; the result is the IEEE quotient bit for bit.
-__device__ __forceinline__ float div_rn(float a, float b, float y) {
-  const float q0 = a * y;
-  const float q1 = fmaf(fmaf(-b, q0, a), y, q0);
-  return fmaf(fmaf(-b, q1, a), y, q1);
-}
-
 // TRACK: keep the winner's barycentrics along the candidate loop, formed
 // from its depth-key products with the resolve's own arithmetic (for stored
 // barycentrics); without it the resolve recomputes them from the winner's
@@ -528,8 +448,7 @@ __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))
                                                    const Rec* __restrict__ rec, const BBox* __restrict__ bbox,
                                                    const int* __restrict__ offs, const int* __restrict__ bins,
                                                    const int* __restrict__ count,
-                                                   long long bin_cap, const unsigned long long* __restrict__ key,
-                                                   long long px_begin, const float* __restrict__ v,
+                                                   long long bin_cap, const float* __restrict__ v,
                                                    const int32_t* __restrict__ tri, int32_t* __restrict__ tri_id,
                                                    float* __restrict__ depth, float* __restrict__ bary,
                                                    long long* __restrict__ status, const float* __restrict__ attr,
@@ -568,8 +487,7 @@ __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))
     if (count[g] != 0) atomicAdd((unsigned long long*)status + 6, 1ull);
   }
 
-  // key: the small-triangle pass's result, or NULL when that pass is off
-  unsigned long long best = inside && key ? key[vw.px_off - px_begin + (long long)py * vw.W + px] : 0ull;
+  unsigned long long best = 0ull;
   // the current winner's barycentrics when it came from this loop, from its
   // products e_k q_k with the resolve's arithmetic: no gather afterwards
   float wb0 = 0.f, wb1 = 0.f;
@@ -752,8 +670,7 @@ __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))
   if (TRACK || out) {
     float b0 = 0.f, b1 = 0.f;
     if (t >= 0) {
-      // a winner not tracked here (small-triangle pass, or no tracking): the
-      // same products from its vertices
+      // a winner not tracked: the same products from its vertices
       if (TRACK && own) {
         b0 = wb0;
         b1 = wb1;
@@ -769,55 +686,9 @@ __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))
       bary[2 * p] = b0;
       bary[2 * p + 1] = b1;
     }
-    if (out) {
-      // interpolation, with the arithmetic of the interpolation kernel, four
-      // channels a load and a store where the channel counts allow
-      const int C = C_a + append_z;
-      float* o = out + p * C;
-      const int vout = row_vec(C, out);
-      const bool a_al = ((vw.a_off * C_a) & 3) == 0;
-      const int va = row_vec(C_a, attr) == 3 ? 3 : row_vec(C_a, attr) == 4 && a_al ? 4 : 0;
-      float b2 = 0.f, zv = 0.f;
-      const float *a0 = attr, *a1 = attr, *a2 = attr;
-      if (t >= 0) {
-        b2 = (1.0f - b0) - b1;
-        const int32_t* row = tri_row(tri, vw, t);
-        const int i0 = row[0], i1 = row[1], i2 = row[2];
-        a0 = attr + (vw.a_off + i0) * C_a;
-        a1 = attr + (vw.a_off + i1) * C_a;
-        a2 = attr + (vw.a_off + i2) * C_a;
-        if (append_z) {
-          const float* vb = v + vw.v_off * 3;
-          const float z0 = vb[(size_t)i0 * 3 + 2], z1 = vb[(size_t)i1 * 3 + 2], z2 = vb[(size_t)i2 * 3 + 2];
-          zv = (b0 * z0 + b1 * z1) + b2 * z2;
-        }
-      }
-      for (int c0 = 0; c0 < C; c0 += 4) {
-        const int n = min(4, C - c0);
-        float xs[4] = {0.f, 0.f, 0.f, 0.f};
-        if (t >= 0) {
-          if (c0 < C_a) {
-            const int na = min(4, C_a - c0);
-            const float4 x0 = row4(a0 + c0, va, na), x1 = row4(a1 + c0, va, na), x2 = row4(a2 + c0, va, na);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (j < na) xs[j] = (b0 * f4(x0, j) + b1 * f4(x1, j)) + b2 * f4(x2, j);
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (append_z && c0 + j == C_a) xs[j] = zv;
-        }
-        if (vout == 4) {
-          *reinterpret_cast<float4*>(o + c0) = make_float4(xs[0], xs[1], xs[2], xs[3]);
-        } else if (vout == 3) {
-          *reinterpret_cast<float3*>(o + c0) = make_float3(xs[0], xs[1], xs[2]);
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (j < n) o[c0 + j] = xs[j];
-        }
-      }
-    }
+    if (out)
+      resolve_attr({v, tri, tri_id, depth, bary, attr, C_a, append_z, out}, vw, p, t, b0, b1,
+                   tri_row(tri, vw, max(t, 0)));
   }
 }
 
@@ -825,6 +696,7 @@ __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))
 int launch_rasterize(const mer_plan* P, const mer_view* views, const float* v, const int32_t* tri, int32_t* tri_id,
                      float* depth, float* bary, const float* attr, int C_a, int append_z, float* out, void* ws,
                      hipStream_t st) {
+  if (P->small_px > 0) return launch_coarse(P, views, {v, tri, tri_id, depth, bary, attr, C_a, append_z, out}, ws, st);
   char* w = (char*)ws;
   long long* viewtab = (long long*)(w + P->off_viewtab);
   long long* tri_base = viewtab;
@@ -841,21 +713,15 @@ int launch_rasterize(const mer_plan* P, const mer_view* views, const float* v, c
   int* big_off = big_n + P->n_bingroups;  // n_bingroups + 1 entries
   long long* big_part = (long long*)(w + P->off_bigpart);
   int* big_flat = (int*)(w + P->off_bigflat);
-  unsigned long long* key = (unsigned long long*)(w + P->off_key);
-  const long long npx = P->total_px - P->px_begin;
   const int twl = __builtin_ctz(P->tile_w), thl = __builtin_ctz(P->tile_h);
 
   hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, twl, thl, tri_base, tile_base, status);
   const long long nt = P->total_tiles;
   hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)min((nt + 255) / 256, 4096ll)), dim3(256), 0, st, count, nt);
-  if (P->small_px > 0)
-    hipLaunchKernelGGL(k_zero_u64, dim3((unsigned)min((npx + 255) / 256, 8192ll)), dim3(256), 0, st, key, npx);
-  else
-    key = nullptr;  // no small-triangle pass: every pixel starts from background
   if (P->total_tris > 0) {
     const dim3 bgrid((unsigned)((P->total_tris + kBinBlock - 1) / kBinBlock)), bblock(kBinBlock);
     hipLaunchKernelGGL(k_setup, bgrid, bblock, 0, st, views, P->n_views, v, tri, tri_base, tile_base, P->total_tris,
-                       twl, thl, P->small_px, (int)P->big_tiles, P->px_begin, rec, bbox, count, key, status, big,
+                       twl, thl, (int)P->big_tiles, rec, bbox, count, status, big,
                        big_n);
     const long long nl = bgrid.x, nlp = (nl + 1023) / 1024;  // list lengths -> offsets, total in status[4]
     hipLaunchKernelGGL(k_scan_partial, dim3((unsigned)nlp), dim3(256), 0, st, big_n, nl, big_part);
@@ -879,12 +745,12 @@ int launch_rasterize(const mer_plan* P, const mer_view* views, const float* v, c
   do {                                                                                                   \
     if (bary)                                                                                            \
       hipLaunchKernelGGL((k_raster<TW, TH, true>), dim3((unsigned)nt), dim3(TW * TH), 0, st, views,      \
-                         P->n_views, tri_base, tile_base, rec, bbox, offs, bins, count, P->bin_cap, key, \
-                         P->px_begin, v, tri, tri_id, depth, bary, status, attr, C_a, append_z, out);    \
+                         P->n_views, tri_base, tile_base, rec, bbox, offs, bins, count, P->bin_cap, v,   \
+                         tri, tri_id, depth, bary, status, attr, C_a, append_z, out);                    \
     else                                                                                                 \
       hipLaunchKernelGGL((k_raster<TW, TH, false>), dim3((unsigned)nt), dim3(TW * TH), 0, st, views,     \
-                         P->n_views, tri_base, tile_base, rec, bbox, offs, bins, count, P->bin_cap, key, \
-                         P->px_begin, v, tri, tri_id, depth, bary, status, attr, C_a, append_z, out);    \
+                         P->n_views, tri_base, tile_base, rec, bbox, offs, bins, count, P->bin_cap, v,   \
+                         tri, tri_id, depth, bary, status, attr, C_a, append_z, out);                    \
   } while (0)
   if (P->tile_w == 8 && P->tile_h == 8) MER_RASTER(8, 8);
   else if (P->tile_w == 16 && P->tile_h == 16) MER_RASTER(16, 16);
