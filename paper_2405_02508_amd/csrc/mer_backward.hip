@@ -238,8 +238,11 @@ __device__ __forceinline__ int slot_of(int* s_key, int* s_list, int* s_nocc, int
 }
 
 // L2: dL/d(img) = 2 w (img - target) is formed here instead of read from g.
-// LOSS: w * sum (img - target)^2 over each wave's 64 pixels goes to
-// loss_part[4 tile + wave] (computed last, when few registers are live).
+// LOSS: w * sum (img - target)^2 over the tile's pixels goes to
+// loss_part[tile].  Its rows are read first, four channels a load, while the
+// index image is on its way; one load per channel after the sweep, when most
+// rows have left the cache, took longer than the sweep (64 head views, 8
+// channels: 1.96 ms before, 1.00 now; reading both images alone takes 0.6).
 template <bool L2, bool LOSS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k_backward(const mer_view* __restrict__ views, int n_views,
                                                   const long long* __restrict__ btile_base,
@@ -259,6 +262,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
   // are neighbours of its border pixels (16 per side: left, right, up, down)
   __shared__ int s_t[kQ];
   __shared__ unsigned char s_cm[kQ];
+  __shared__ float s_loss[4];
   // the table starts empty and zero: a run end may raise a slot's maximum as
   // soon as another lane has claimed the slot
   for (int i = threadIdx.x; i < kSlots; i += blockDim.x) s_key[i] = -1;
@@ -267,9 +271,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
   if (threadIdx.x == 0) s_nocc = 0;
 
   const long long tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int vi = __builtin_amdgcn_readfirstlane(find_bucket(btile_base, n_views, tile));
+  long long local_tile;
+  const int vi = tile_view(btile_base, n_views, tile, local_tile);
   const mer_view vw = views[vi];
-  const long long local_tile = tile - btile_base[vi];
   const int tiles_x = (vw.W + 15) >> 4;
   int x0, y0;
   grid_xy(local_tile, tiles_x, x0, y0);
@@ -289,6 +293,23 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
   const bool v2img = (C_e & 1) == 0 && ((uintptr_t)img & 7) == 0;
   const bool v2tar = L2 && (C_e & 1) == 0 && ((uintptr_t)target & 7) == 0;
   const bool v2g = !L2 && (ld_g & 1) == 0 && ((uintptr_t)g & 7) == 0;
+
+  if constexpr (LOSS) {
+    float e2 = 0.f;
+    if (inside)
+      for (int c0 = 0; c0 < C_e; c0 += 4) {
+        const int n = min(4, C_e - c0);
+        const float4 a = row4(img + p * C_e + c0, vimg, n), b = row4(target + p * C_e + c0, vtar, n);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (j < n) {
+            const float d = f4(a, j) - f4(b, j);
+            e2 += d * d;
+          }
+      }
+    e2 = wave_sum_f32(e2);
+    if (lane == 63) s_loss[threadIdx.x >> 6] = e2;
+  }
 
   // ---- the ring, by the first wave: each lane one ring pixel.  Its id, and
   // whether its triangle holds the centre of its neighbour in the tile (as
@@ -328,6 +349,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
   s_t[lt] = t_id;
   s_cm[lt] = (unsigned char)cm;
   __syncthreads();
+  if constexpr (LOSS)
+    if (lt == 0) loss_part[tile] = w_l2 * ((s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]));
 
   // ---- micro-edge term: fragment gradient (rx, ry, rq) of this pixel.
   // A background pixel is never the top side of a pair, so it receives
@@ -679,17 +702,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
       atomicAdd(g_attr + (vw.a_off + key) * C_a + (j - 3), x);
     }
   }
-  if constexpr (LOSS) {
-    float e2 = 0.f;
-    if (inside)
-      for (int c = 0; c < C_e; ++c) {
-        const float d = img[p * C_e + c] - target[p * C_e + c];
-        e2 += d * d;
-      }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) e2 += __shfl_xor(e2, o, 64);
-    if (lane == 0) loss_part[4 * tile + (threadIdx.x >> 6)] = w_l2 * e2;
-  }
 }
 
 int launch_interpolate(const mer_plan* P, const mer_view* views, const float* attr, int C_a, const float* v,
@@ -704,20 +716,33 @@ int launch_interpolate(const mer_plan* P, const mer_view* views, const float* at
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }
 
-// Sum of the per-tile loss partials, one workgroup, then one atomic.
+// Sum of the per-tile loss partials in binary64, one workgroup, then one
+// atomic.  Each thread has eight 16-byte loads in flight (the partials come
+// from the other XCDs, a few microseconds away): 172,000 partials of the 64
+// head views take 24 us; one 4-byte load at a time, over one partial per wave,
+// took 280.  part is 16-byte aligned.
 __global__ void __launch_bounds__(1024) k_loss_sum(const float* __restrict__ part, long long n,
                                                    float* __restrict__ loss) {
-  __shared__ float s_w[16];
-  float a = 0.f;
-  for (long long i = threadIdx.x; i < n; i += blockDim.x) a += part[i];
+  __shared__ double s_w[16];
+  double a = 0.0;
+  const long long n4 = n >> 2;
+  const float4* p4 = reinterpret_cast<const float4*>(part);
+  for (long long i = threadIdx.x; i < n4; i += 8 * 1024) {
+    float4 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = i + j * 1024 < n4 ? p4[i + j * 1024] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) a += ((double)x[j].x + (double)x[j].y) + ((double)x[j].z + (double)x[j].w);
+  }
+  if (threadIdx.x < (n & 3)) a += (double)part[4 * n4 + threadIdx.x];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
   if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = a;
   __syncthreads();
   if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) t += s_w[i];
-    atomicAdd(loss, t);
+    double t = 0.0;
+    for (int i = 0; i < 16; ++i) t += s_w[i];
+    atomicAdd(loss, (float)t);
   }
 }
 
@@ -726,18 +751,21 @@ int launch_backward(const mer_plan* P, const mer_view* views, const float* v, co
                     const float* g, const float* target, float w_l2, float* loss, int C_e, int ld_g, int flags,
                     float* g_attr, float* g_v, long long* tab, float* loss_part, hipStream_t st) {
   float* bloss = loss ? loss_part : nullptr;
-  // 16x16 tile prefix per view; the rasterizer's status words are left alone
-  hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, 4, 4, tab, tab + (P->n_views + 1),
-                     (long long*)nullptr);
+  // 16x16 tile prefix per view (one view needs none); the rasterizer's status
+  // words are left alone
+  const long long* base = P->n_views > 1 ? tab + (P->n_views + 1) : nullptr;
+  if (base)
+    hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, 4, 4, tab, tab + (P->n_views + 1),
+                       (long long*)nullptr);
 #define MER_BACKWARD(L2, LOSS)                                                                                 \
   hipLaunchKernelGGL((k_backward<L2, LOSS>), dim3((unsigned)P->total_btiles), dim3(256), 0, st, views, P->n_views, \
-                     tab + (P->n_views + 1), v, tri, tri_id, attr, C_a, append_z, img, g, C_e, ld_g, flags, g_attr,  \
-                     g_v, target, w_l2, bloss)
+                     base, v, tri, tri_id, attr, C_a, append_z, img, g, C_e, ld_g, flags, g_attr, g_v, target, w_l2, \
+                     bloss)
   if (!target) MER_BACKWARD(false, false);
   else if (!bloss) MER_BACKWARD(true, false);
   else MER_BACKWARD(true, true);
 #undef MER_BACKWARD
-  if (bloss) hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(1024), 0, st, bloss, 4 * P->total_btiles, loss);
+  if (bloss) hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(1024), 0, st, bloss, P->total_btiles, loss);
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }
 

@@ -629,6 +629,16 @@ __device__ __forceinline__ int wave_bucket(const T* base, int n, long long g) {
   return b;
 }
 
+// View of tile g (uniform) from the tile prefix per view, and the tile's place
+// in it; base is NULL for a plan of one view.
+__device__ __forceinline__ int tile_view(const long long* base, int n_views, long long g, long long& local) {
+  local = g;
+  if (!base) return 0;
+  const int vi = __builtin_amdgcn_readfirstlane(find_bucket(base, n_views, g));
+  local = g - base[vi];
+  return vi;
+}
+
 // View of the wave's first pixel, searched with a wave-uniform index so the
 // loads go through the scalar cache.
 __device__ __forceinline__ int wave_view(const mer_view* views, int n, long long p0) {
@@ -657,6 +667,16 @@ __device__ __forceinline__ unsigned wave_min_u32(unsigned x) {
   return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
 }
 __device__ __forceinline__ unsigned wave_max_u32(unsigned x) { return ~wave_min_u32(~x); }
+// sum over the lanes of a wave, in lane 63
+__device__ __forceinline__ float wave_sum_f32(float x) {
+  x += __int_as_float(dpp_zero<0x111, 0xf>(__float_as_int(x)));
+  x += __int_as_float(dpp_zero<0x112, 0xf>(__float_as_int(x)));
+  x += __int_as_float(dpp_zero<0x114, 0xf>(__float_as_int(x)));
+  x += __int_as_float(dpp_zero<0x118, 0xf>(__float_as_int(x)));
+  x += __int_as_float(dpp_zero<0x142, 0xa>(__float_as_int(x)));
+  x += __int_as_float(dpp_zero<0x143, 0xc>(__float_as_int(x)));
+  return x;
+}
 // inclusive sum over the lanes of a wave
 __device__ __forceinline__ int wave_scan_i32(int x) {
   x += dpp_zero<0x111, 0xf>(x);

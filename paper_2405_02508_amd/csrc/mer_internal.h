@@ -23,8 +23,8 @@ int launch_backface(const mer_plan* P, const mer_view* views, const float* v, co
 // g: dL/d(img) rows of ld_g floats, or NULL with target != NULL for the fused
 // L2 loss (dL/d(img) = 2 w (img - target), loss += w sum (img - target)^2).
 // Scratch: tab, 2 (n_views + 1) int64 (the 16x16 tile prefix per view, written
-// here); loss_part, 4 total_btiles floats (per-wave loss partials, written
-// here; only read when loss != NULL).
+// here; not for one view); loss_part, total_btiles floats (per-tile loss
+// partials, written here; only read when loss != NULL).
 int launch_backward(const mer_plan* P, const mer_view* views, const float* v, const int32_t* tri,
                     const int32_t* tri_id, const float* attr, int C_a, int append_z, const float* img,
                     const float* g, const float* target, float w_l2, float* loss, int C_e, int ld_g, int flags,

@@ -88,12 +88,13 @@ __global__ void __launch_bounds__(TS * TS) __attribute__((amdgpu_waves_per_eu(6)
   // centre (d: 0 left, 1 right, 2 up, 3 down); a border pixel sets only the
   // bit toward its tile neighbour
   __shared__ unsigned char s_cm[TileDims<TS>::G * TileDims<TS>::G];
-  const long long n_tiles = btile_base[n_views];
+  const long long n_tiles = btile_base ? btile_base[n_views]
+                                       : (long long)((views[0].W + TS - 1) / TS) * ((views[0].H + TS - 1) / TS);
   if ((long long)blockIdx.x >= n_tiles) return;  // the grid may hold spare workgroups
   const long long tile = xcd_tile(blockIdx.x, n_tiles);
-  const int vi = __builtin_amdgcn_readfirstlane(find_bucket(btile_base, n_views, tile));
+  long long local_tile;
+  const int vi = tile_view(btile_base, n_views, tile, local_tile);
   const mer_view vw = views[vi];
-  const long long local_tile = tile - btile_base[vi];
   const int tiles_x = (vw.W + TS - 1) / TS;
   int x0, y0;
   grid_xy(local_tile, tiles_x, x0, y0);
@@ -330,12 +331,14 @@ int launch_jvp(const mer_plan* P, const mer_view* views, const float* v, const i
   // words are left alone.  A view has at most 4 times as many of these tiles
   // as 16x16 ones, so 4 workgroups per 16x16 tile cover them all.
   constexpr int TS = 8, lg = 3;
-  hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, lg, lg, tab, tab + (P->n_views + 1),
-                     (long long*)nullptr);
+  const long long* base = P->n_views > 1 ? tab + (P->n_views + 1) : nullptr;
+  if (base)
+    hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, lg, lg, tab, tab + (P->n_views + 1),
+                       (long long*)nullptr);
   const long long grid = P->total_btiles * (16 / TS) * (16 / TS);
   if (grid > 0)
     hipLaunchKernelGGL(k_jvp<TS>, dim3((unsigned)grid), dim3(TS * TS), 0, st, views, P->n_views,
-                       tab + (P->n_views + 1), v, tri, tri_id, attr, dattr, C_a, append_z, img, C_e, dv, flags, dimg);
+                       base, v, tri, tri_id, attr, dattr, C_a, append_z, img, C_e, dv, flags, dimg);
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }
 

@@ -149,9 +149,9 @@ __global__ void __launch_bounds__(256) k_texture_bwd(const mer_view* __restrict_
   __shared__ unsigned long long s_acc[kTexWin];
   __shared__ int s_box[6];  // x min, y min, -x max, -y max, bits of max |g|, any non-finite g
   const long long tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int vi = __builtin_amdgcn_readfirstlane(find_bucket(btile_base, n_views, tile));
+  long long local_tile;
+  const int vi = tile_view(btile_base, n_views, tile, local_tile);
   const mer_view vw = views[vi];
-  const long long local_tile = tile - btile_base[vi];
   const int tiles_x = (vw.W + 15) >> 4;
   int px, py;
   grid_xy(local_tile, tiles_x, px, py);
@@ -349,16 +349,18 @@ int launch_texture_bwd(const mer_plan* P, const mer_view* views, const int32_t* 
                        const float* tex, int th, int tw, int C, const float* g_out, float* g_tex, float* g_uv,
                        void* ws, hipStream_t st) {
   long long* tab = (long long*)((char*)ws + P->off_bviewtab);
-  hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, 4, 4, tab, tab + (P->n_views + 1),
-                     (long long*)nullptr);
+  const long long* base = P->n_views > 1 ? tab + (P->n_views + 1) : nullptr;
+  if (base)
+    hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, 4, 4, tab, tab + (P->n_views + 1),
+                       (long long*)nullptr);
   const bool v4 = C % 4 == 0 && ((uintptr_t)tex % 16) == 0 && ((uintptr_t)g_out % 16) == 0;
   if (P->total_btiles > 0) {
     if (v4)
       hipLaunchKernelGGL(k_texture_bwd<true>, dim3((unsigned)P->total_btiles), dim3(256), 0, st, views, P->n_views,
-                         tab + (P->n_views + 1), tri_id, uv, ld_uv, tex, th, tw, C, g_out, g_tex, g_uv);
+                         base, tri_id, uv, ld_uv, tex, th, tw, C, g_out, g_tex, g_uv);
     else
       hipLaunchKernelGGL(k_texture_bwd<false>, dim3((unsigned)P->total_btiles), dim3(256), 0, st, views, P->n_views,
-                         tab + (P->n_views + 1), tri_id, uv, ld_uv, tex, th, tw, C, g_out, g_tex, g_uv);
+                         base, tri_id, uv, ld_uv, tex, th, tw, C, g_out, g_tex, g_uv);
   }
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }
