@@ -213,8 +213,9 @@ struct Steps {
 //     the last lane of each run adds the run's sums into an LDS table keyed
 //     by vertex (a vertex is shared by the runs of several triangles);
 //  5. the workgroup flushes the table with one global float atomic per
-//     (vertex, component).  Vertices that do not fit the table, and
-//     attribute channels beyond kCTab, go straight to global atomics.
+//     (vertex, component).  Vertices that do not fit the table go straight
+//     to global atomics; attribute rows wider than the table take it again,
+//     eight channels at a time (WIDE).
 constexpr int kSlots = 256;  // vertex slots per workgroup
 constexpr int kCTab = 8;     // attribute channels reduced in LDS (two groups of four)
 constexpr int kNV = 3 + kCTab;
@@ -243,8 +244,10 @@ __device__ __forceinline__ int slot_of(int* s_key, int* s_list, int* s_nocc, int
 // index image is on its way; one load per channel after the sweep, when most
 // rows have left the cache, took longer than the sweep (64 head views, 8
 // channels: 1.96 ms before, 1.00 now; reading both images alone takes 0.6).
-template <bool L2, bool LOSS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k_backward(const mer_view* __restrict__ views, int n_views,
+// WIDE: more attribute channels than the table takes at once; its loop keeps
+// more registers live, so it gets five waves per SIMD instead of seven.
+template <bool L2, bool LOSS, bool WIDE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 5 : 7))) k_backward(const mer_view* __restrict__ views, int n_views,
                                                   const long long* __restrict__ btile_base,
                                                   const float* __restrict__ v, const int32_t* __restrict__ tri,
                                                   const int32_t* __restrict__ tri_id, const float* __restrict__ attr,
@@ -560,22 +563,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
     fy -= sy;
   }
   const bool attr_tab = want_interp && g_attr;
-  if (attr_tab) {
-    // channels past the table's go straight to memory
-    for (int c0 = kCTab; c0 < C_a; c0 += 4) {
-      float sm[12];
-#pragma unroll
-      for (int i = 0; i < 12; ++i) sm[i] = 0.f;
-      dispatch([&](auto steps) { attr_sums(steps, c0, sm); });
-      if (emit)
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (c0 + j < C_a && sm[4 * k + j] != 0.f)
-              atomicAdd(g_attr + (vw.a_off + S.idx[k]) * C_a + c0 + j, sm[4 * k + j]);
-    }
-  }
   // the run sums the table takes: vertex k's (x, y, z) gradient at 3 k, and
   // its channels 0-3 and 4-7 at 4 k + j
   float sv[9], sa0[12], sa1[12];
@@ -702,6 +689,72 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
       atomicAdd(g_attr + (vw.a_off + key) * C_a + (j - 3), x);
     }
   }
+  if constexpr (WIDE) {
+    // ---- channels 8 on: the table again, eight at a time, same slots.  Added
+    // to memory by each run end instead, scattered over the vertices' rows,
+    // channels 8 to 15 of four 731 x 413 views took 320 of the adjoint's
+    // 350 us; the whole adjoint takes 43 this way.
+    for (int cb = kCTab; attr_tab && cb < C_a; cb += kCTab) {
+      __syncthreads();  // the last round's sums are flushed
+      for (int i = threadIdx.x; i < kSlots * kNV / 4; i += blockDim.x) reinterpret_cast<int4*>(s_acc)[i] = make_int4(0, 0, 0, 0);
+      for (int i = threadIdx.x; i < kSlots * 3 / 4; i += blockDim.x) reinterpret_cast<uint4*>(s_mx)[i] = make_uint4(0u, 0u, 0u, 0u);
+      __syncthreads();
+      const bool two = C_a > cb + 4;
+#pragma unroll
+      for (int i = 0; i < 12; ++i) sa0[i] = sa1[i] = 0.f;
+      dispatch([&](auto steps) {
+        attr_sums(steps, cb, sa0);
+        if (two) attr_sums(steps, cb + 4, sa1);
+      });
+      if (emit) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          unsigned m1 = 0u, m2 = 0u;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            m1 = max(m1, __float_as_uint(sa0[4 * k + j]) & 0x7fffffffu);
+            m2 = max(m2, __float_as_uint(sa1[4 * k + j]) & 0x7fffffffu);
+          }
+          if (slot[k] < 0) continue;
+          atomicMax(&s_mx[__umul24(slot[k], 3) + 1], m1);
+          if (two) atomicMax(&s_mx[__umul24(slot[k], 3) + 2], m2);
+        }
+      }
+      __syncthreads();  // the maxima are final
+      if (emit) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+#pragma unroll
+          for (int grp = 1; grp < 3; ++grp) {
+            if (grp == 2 && !two) continue;
+            const unsigned M = slot[k] >= 0 ? s_mx[slot[k] * 3 + grp] : 0x7f800000u;
+            int E = 0;
+            (void)frexpf(__uint_as_float(M), &E);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float x = grp == 1 ? sa0[4 * k + j] : sa1[4 * k + j];
+              const int c = cb + 4 * (grp - 1) + j;
+              if (M < 0x7f800000u)
+                atomicAdd(&s_acc[__umul24(slot[k], kNV) + 4 * grp - 1 + j], round_half_up(ldexpf(x, 22 - E)));
+              else if (x != 0.f && c < C_a)
+                atomicAdd(g_attr + (vw.a_off + S.idx[k]) * C_a + c, x);
+            }
+          }
+        }
+      }
+      __syncthreads();
+      const int nch = min(C_a - cb, kCTab);
+      for (int k = threadIdx.x; k < nocc * nch; k += blockDim.x) {
+        const int i = k / nch, j = k - i * nch;
+        const int s = s_list[i];
+        const int qv = s_acc[s * kNV + 3 + j];
+        if (qv == 0) continue;
+        int E = 0;
+        (void)frexpf(__uint_as_float(s_mx[s * 3 + (j < 4 ? 1 : 2)]), &E);
+        atomicAdd(g_attr + (vw.a_off + s_key[s]) * C_a + cb + j, ldexpf((float)qv, E - 22));
+      }
+    }
+  }
 }
 
 int launch_interpolate(const mer_plan* P, const mer_view* views, const float* attr, int C_a, const float* v,
@@ -757,14 +810,21 @@ int launch_backward(const mer_plan* P, const mer_view* views, const float* v, co
   if (base)
     hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, 4, 4, tab, tab + (P->n_views + 1),
                        (long long*)nullptr);
-#define MER_BACKWARD(L2, LOSS)                                                                                 \
-  hipLaunchKernelGGL((k_backward<L2, LOSS>), dim3((unsigned)P->total_btiles), dim3(256), 0, st, views, P->n_views, \
+  const bool wide = C_a > kCTab && g_attr && !(flags & MER_SKIP_INTERP);
+#define MER_BACKWARD_W(L2, LOSS, WIDE)                                                                         \
+  hipLaunchKernelGGL((k_backward<L2, LOSS, WIDE>), dim3((unsigned)P->total_btiles), dim3(256), 0, st, views, P->n_views, \
                      base, v, tri, tri_id, attr, C_a, append_z, img, g, C_e, ld_g, flags, g_attr, g_v, target, w_l2, \
                      bloss)
+#define MER_BACKWARD(L2, LOSS)                 \
+  do {                                         \
+    if (wide) MER_BACKWARD_W(L2, LOSS, true);  \
+    else MER_BACKWARD_W(L2, LOSS, false);      \
+  } while (0)
   if (!target) MER_BACKWARD(false, false);
   else if (!bloss) MER_BACKWARD(true, false);
   else MER_BACKWARD(true, true);
 #undef MER_BACKWARD
+#undef MER_BACKWARD_W
   if (bloss) hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(1024), 0, st, bloss, P->total_btiles, loss);
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }
