@@ -126,17 +126,32 @@ __global__ void __launch_bounds__(256) k_texture(const mer_view* __restrict__ vi
 // the sums stay below 2^61, each contribution is rounded by at most
 // 2^(e - 52) <= 2^-51 M, and the sum is exact and independent of order.  A
 // tile with a non-finite dL/d(out) adds straight to memory instead.
+//
+// Bound now by the L2's float atomics: a 16 x 16 tile at one texel per pixel
+// flushes about 160 requests of 16 floats, 15.5 M on 96 scenes (35.8 M px),
+// 0.8 ms at the 19.2 G/s that a plain kernel of atomic adds reaches; the
+// kernel takes 0.94 ms, 1.28 when it formed each contribution in five
+// operations, reduced the tile's box through LDS and divided in the flush.
 constexpr int kTexWin = 3072;
 
-// round(x s) to the nearest integer (ties to even) for |x s| < 2^51, as the
-// bits of a 64-bit integer: x s + 1.5 2^52 lies in [2^52, 2^53), where the
-// binary64 spacing is 1, so the one rounding of the fused multiply-add is
-// the rounding to an integer, and the integer is the difference of the sum's
-// bits and the constant's
-__device__ __forceinline__ unsigned long long fixed_round(float x, double s) {
+// round(w g) to the nearest integer (ties to even) for |w g| < 2^51, as the
+// bits of a 64-bit integer: w g + 1.5 2^52 lies in [2^52, 2^53), where the
+// binary64 spacing is 1, so the one rounding of the fused multiply-add (the
+// product is exact in it) is the rounding to an integer, and the integer is
+// the difference of the sum's bits and the constant's, whose low word is 0.
+// w is the weight times the tile's scale, g the gradient, both in binary64:
+// two operations per contribution where forming w g in binary32, converting
+// and subtracting 64 bits took five.
+__device__ __forceinline__ unsigned long long fixed_round(double w, double g) {
   const double magic = 6755399441055744.0;  // 1.5 * 2^52
-  return (unsigned long long)(__double_as_longlong(fma((double)x, s, magic)) - __double_as_longlong(magic));
+  const unsigned long long bits = (unsigned long long)__double_as_longlong(fma(w, g, magic));
+  return (unsigned long long)((unsigned)(bits >> 32) - 0x43380000u) << 32 | (unsigned)bits;
 }
+
+// floor(i / d) for i < 2^16, 2 <= d < 2^16 by a high product with
+// m = ceil(2^32 / d): i (m d - 2^32) < 2^32.  d = 1 has m = 0.
+__device__ __forceinline__ unsigned div_magic(unsigned d) { return d > 1 ? 0xffffffffu / d + 1u : 0u; }
+__device__ __forceinline__ unsigned div_by(unsigned i, unsigned m) { return m ? __umulhi(i, m) : i; }
 
 template <bool V4>
 __global__ void __launch_bounds__(256) k_texture_bwd(const mer_view* __restrict__ views, int n_views,
@@ -146,8 +161,9 @@ __global__ void __launch_bounds__(256) k_texture_bwd(const mer_view* __restrict_
                                                      const float* __restrict__ tex, int th, int tw, int C,
                                                      const float* __restrict__ g_out, float* __restrict__ g_tex,
                                                      float* __restrict__ g_uv) {
-  __shared__ unsigned long long s_acc[kTexWin];
-  __shared__ int s_box[6];  // x min, y min, -x max, -y max, bits of max |g|, any non-finite g
+  __shared__ __align__(16) unsigned long long s_acc[kTexWin];
+  __shared__ int4 s_box[4];        // per wave: x min, y min, x max, y max
+  __shared__ unsigned s_gmax[4];   // per wave: bits of max |g|
   const long long tile = xcd_tile(blockIdx.x, gridDim.x);
   long long local_tile;
   const int vi = tile_view(btile_base, n_views, tile, local_tile);
@@ -159,30 +175,33 @@ __global__ void __launch_bounds__(256) k_texture_bwd(const mer_view* __restrict_
   py = py * 16 + (threadIdx.x >> 4);
   const bool inside = px < vw.W && py < vw.H;
   const long long p = vw.px_off + (long long)py * vw.W + px;
-  if (threadIdx.x < 4) s_box[threadIdx.x] = 0x7fffffff;
-  if (threadIdx.x == 4 || threadIdx.x == 5) s_box[threadIdx.x] = 0;
 
-  const bool want = inside && (!tri_id || tri_id[p] >= 0);
-  const TexCell cell = tex_cell(want, want ? uv[p * ld_uv] : 0.f, want ? uv[p * ld_uv + 1] : 0.f, th, tw);
+  const long long pc = inside ? p : vw.px_off;
+  const int tid = inside && tri_id ? tri_id[p] : 0;
+  const bool want = inside && tid >= 0;
+  const TexCell cell = tex_cell(want, uv[pc * ld_uv], uv[pc * ld_uv + 1], th, tw);
   const float* g = g_out + (cell.ok ? p : 0) * C;
   const float w00 = (1.0f - cell.fx) * (1.0f - cell.fy), w10 = cell.fx * (1.0f - cell.fy);
   const float w01 = (1.0f - cell.fx) * cell.fy, w11 = cell.fx * cell.fy;
   const long long r00 = ((long long)cell.y[0] * tw + cell.x[0]) * C, r10 = ((long long)cell.y[0] * tw + cell.x[1]) * C;
   const long long r01 = ((long long)cell.y[1] * tw + cell.x[0]) * C, r11 = ((long long)cell.y[1] * tw + cell.x[1]) * C;
 
-  float gmax = 0.f;
-  bool gbad = false;
-  if (g_uv && inside) {
-    float du = 0.f, dv = 0.f;
-    if (cell.ok) {
-      if constexpr (V4) {
-        for (int c = 0; c < C; c += 4) {
-          const float4 gg = *reinterpret_cast<const float4*>(g + c);
+  // dL/duv and the largest |dL/d(out)| in one pass over the channels (an
+  // infinity or NaN sorts above every finite value by its bits)
+  unsigned gmax = 0u;
+  float du = 0.f, dv = 0.f;
+  if (cell.ok) {
+    if constexpr (V4) {
+      for (int c = 0; c < C; c += 4) {
+        const float4 gg = *reinterpret_cast<const float4*>(g + c);
+        const float gs[4] = {gg.x, gg.y, gg.z, gg.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) gmax = max(gmax, __float_as_uint(gs[k]) & 0x7fffffffu);
+        if (g_uv) {
           const float4 a = *reinterpret_cast<const float4*>(tex + r00 + c);
           const float4 b = *reinterpret_cast<const float4*>(tex + r10 + c);
           const float4 d = *reinterpret_cast<const float4*>(tex + r01 + c);
           const float4 f = *reinterpret_cast<const float4*>(tex + r11 + c);
-          const float gs[4] = {gg.x, gg.y, gg.z, gg.w};
           const float t00[4] = {a.x, a.y, a.z, a.w}, t10[4] = {b.x, b.y, b.z, b.w};
           const float t01[4] = {d.x, d.y, d.z, d.w}, t11[4] = {f.x, f.y, f.z, f.w};
 #pragma unroll
@@ -191,56 +210,49 @@ __global__ void __launch_bounds__(256) k_texture_bwd(const mer_view* __restrict_
             dv += gs[k] * ((1.0f - cell.fx) * (t01[k] - t00[k]) + cell.fx * (t11[k] - t10[k]));
           }
         }
-      } else {
-        for (int c = 0; c < C; ++c) {
+      }
+    } else {
+      for (int c = 0; c < C; ++c) {
+        gmax = max(gmax, __float_as_uint(g[c]) & 0x7fffffffu);
+        if (g_uv) {
           const float t00 = tex[r00 + c], t10 = tex[r10 + c], t01 = tex[r01 + c], t11 = tex[r11 + c];
           du += g[c] * ((1.0f - cell.fy) * (t10 - t00) + cell.fy * (t11 - t01));
           dv += g[c] * ((1.0f - cell.fx) * (t01 - t00) + cell.fx * (t11 - t10));
         }
       }
     }
+  }
+  if (g_uv && inside) {
     g_uv[2 * p] = du * (float)tw;
     g_uv[2 * p + 1] = dv * (float)th;
   }
   if (!g_tex) return;  // uniform: every thread leaves before the barriers
-  if (cell.ok)
-    for (int c = 0; c < C; ++c) {
-      const float a = fabsf(g[c]);
-      gbad |= !(a <= 3.40282347e38f);  // inf or NaN
-      gmax = fmaxf(gmax, a);
-    }
 
-  // per-wave reductions (every lane takes part), then one atomic per wave
-  const int big = 0x7fffffff;
-  int r0 = cell.ok ? cell.x[0] : big, r1 = cell.ok ? cell.y[0] : big;
-  int r2 = cell.ok ? -cell.x[1] : big, r3 = cell.ok ? -cell.y[1] : big;
-  int r4 = __float_as_int(gmax), r5 = gbad ? 1 : 0;  // gmax >= 0: its bits order like its value
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    r0 = min(r0, __shfl_xor(r0, o, 64));
-    r1 = min(r1, __shfl_xor(r1, o, 64));
-    r2 = min(r2, __shfl_xor(r2, o, 64));
-    r3 = min(r3, __shfl_xor(r3, o, 64));
-    r4 = max(r4, __shfl_xor(r4, o, 64));
-    r5 = r5 | __shfl_xor(r5, o, 64);
-  }
-  __syncthreads();  // s_box initialised
+  // the tile's box of texels and largest |dL/d(out)|: a reduction per wave in
+  // registers, then the four waves' values (texel indices are below 2^31)
+  const unsigned far = 0x7fffffffu;
+  const unsigned bx = wave_min_u32(cell.ok ? (unsigned)cell.x[0] : far), by = wave_min_u32(cell.ok ? (unsigned)cell.y[0] : far);
+  const unsigned ex = wave_max_u32(cell.ok ? (unsigned)cell.x[1] : 0u), ey = wave_max_u32(cell.ok ? (unsigned)cell.y[1] : 0u);
+  const unsigned gm = wave_max_u32(gmax);
   if ((threadIdx.x & 63) == 0) {
-    atomicMin(&s_box[0], r0);
-    atomicMin(&s_box[1], r1);
-    atomicMin(&s_box[2], r2);
-    atomicMin(&s_box[3], r3);
-    atomicMax(&s_box[4], r4);
-    if (r5) atomicOr(&s_box[5], 1);
+    s_box[threadIdx.x >> 6] = make_int4((int)bx, (int)by, (int)ex, (int)ey);
+    s_gmax[threadIdx.x >> 6] = gm;
   }
   __syncthreads();
-  const int bx0 = s_box[0], by0 = s_box[1];
+  int4 box = s_box[0];
+  unsigned Mb = s_gmax[0];
+#pragma unroll
+  for (int i = 1; i < 4; ++i) {
+    const int4 o = s_box[i];
+    box = make_int4(min(box.x, o.x), min(box.y, o.y), max(box.z, o.z), max(box.w, o.w));
+    Mb = max(Mb, s_gmax[i]);
+  }
+  const int bx0 = box.x, by0 = box.y;
   const bool any = bx0 != 0x7fffffff;
-  const long long bw = any ? (long long)(-s_box[2]) - bx0 + 1 : 0, bh = any ? (long long)(-s_box[3]) - by0 + 1 : 0;
+  if (!any || Mb == 0u) return;  // nothing to add (uniform)
+  const long long bw = (long long)box.z - bx0 + 1, bh = (long long)box.w - by0 + 1;
   const long long nwin = bw * bh * C;
-  const float M = __int_as_float(s_box[4]);
-  if (!any || M == 0.f) return;  // nothing to add (uniform)
-  if (nwin > kTexWin || s_box[5]) {
+  if (nwin > kTexWin || Mb >= 0x7f800000u) {
     // Straight to memory (uniform: the whole workgroup is here).  Each wave
     // stages its pixels' four (texel row, weight) pairs in the window's LDS,
     // then adds them channel-fastest: lanes l and l + 1 take channels c and
@@ -277,27 +289,28 @@ __global__ void __launch_bounds__(256) k_texture_bwd(const mer_view* __restrict_
     return;
   }
   int e;
-  frexpf(M, &e);  // M < 2^e
+  frexpf(__uint_as_float(Mb), &e);  // M < 2^e
   const int sh = 51 - e;
   const double scale = ldexp(1.0, sh);
-  for (int i = threadIdx.x; i < (int)nwin; i += blockDim.x) s_acc[i] = 0ull;
+  for (int i = threadIdx.x; i < ((int)nwin + 1) / 2; i += blockDim.x) reinterpret_cast<int4*>(s_acc)[i] = make_int4(0, 0, 0, 0);
   __syncthreads();
   // channel-major window (value c of texel i at c * ncell + i): the lanes of
   // a wave touch neighbouring texels, which then sit 8 bytes apart in LDS
   // rather than C * 8 bytes (with C = 8, four banks for the whole wave)
-  const int ncell = (int)(bw * bh);
+  const int ncell = (int)(bw * bh), bwi = (int)bw;
   if (cell.ok) {
-    const int l00 = (int)((cell.y[0] - by0) * bw + (cell.x[0] - bx0));
-    const int l10 = (int)((cell.y[0] - by0) * bw + (cell.x[1] - bx0));
-    const int l01 = (int)((cell.y[1] - by0) * bw + (cell.x[0] - bx0));
-    const int l11 = (int)((cell.y[1] - by0) * bw + (cell.x[1] - bx0));
-    // |w g 2^sh| < 2^51: exact in binary64, rounded to the nearest integer
+    const int l00 = (cell.y[0] - by0) * bwi + (cell.x[0] - bx0), l10 = l00 + (cell.x[1] - cell.x[0]);
+    const int down = (cell.y[1] - cell.y[0]) * bwi, l01 = l00 + down, l11 = l10 + down;
+    // |w g 2^sh| < 2^51: the product is exact in the multiply-add, rounded to
+    // the nearest integer by it
+    const double d00 = (double)w00 * scale, d10 = (double)w10 * scale, d01 = (double)w01 * scale, d11 = (double)w11 * scale;
     auto add = [&](int c, float gc) {
       unsigned long long* a = s_acc + c * ncell;
-      atomicAdd(a + l00, fixed_round(w00 * gc, scale));
-      atomicAdd(a + l10, fixed_round(w10 * gc, scale));
-      atomicAdd(a + l01, fixed_round(w01 * gc, scale));
-      atomicAdd(a + l11, fixed_round(w11 * gc, scale));
+      const double gd = (double)gc;
+      atomicAdd(a + l00, fixed_round(d00, gd));
+      atomicAdd(a + l10, fixed_round(d10, gd));
+      atomicAdd(a + l01, fixed_round(d01, gd));
+      atomicAdd(a + l11, fixed_round(d11, gd));
     };
     if constexpr (V4) {
       // the row four channels a load, every load issued before the adds
@@ -320,13 +333,16 @@ __global__ void __launch_bounds__(256) k_texture_bwd(const mer_view* __restrict_
     }
   }
   __syncthreads();
-  // the flush walks texel-major, so a wave's global atomics stay contiguous
-  for (int i = threadIdx.x; i < (int)nwin; i += blockDim.x) {
-    const int c = i % C, cell_i = i / C;
-    const long long q = (long long)s_acc[c * ncell + cell_i];
+  // the flush walks texel-major, so a wave's global atomics stay contiguous;
+  // 32-bit divisions by the channel count and the box width as products
+  const unsigned mC = div_magic((unsigned)C), mW = div_magic((unsigned)bwi);
+  float* gt = g_tex + ((long long)by0 * tw + bx0) * C;
+  for (unsigned i = threadIdx.x; i < (unsigned)nwin; i += blockDim.x) {
+    const unsigned ci = div_by(i, mC), c = i - ci * (unsigned)C;
+    const long long q = (long long)s_acc[c * (unsigned)ncell + ci];
     if (q == 0) continue;
-    const long long ty = by0 + cell_i / bw, tx = bx0 + cell_i % bw;
-    atomicAdd(g_tex + (ty * tw + tx) * C + c, (float)ldexp((double)q, -sh));
+    const unsigned y = div_by(ci, mW), x = ci - y * (unsigned)bwi;
+    atomicAdd(gt + ((long long)y * tw + x) * C + c, (float)ldexp((double)q, -sh));
   }
 }
 
