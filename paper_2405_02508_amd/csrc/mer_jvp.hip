@@ -5,10 +5,8 @@
 // classification (Sec. 4.2-4.4), with the edge position's tangent in place of
 // dL/dp, plus the forward derivative of the interpolation (Sec. 3, the smooth
 // term).  One thread per pixel gathers the pairs it belongs to, so every
-// output element is written once, with no atomics; the triangles a tile
-// needs are snapped once into LDS.
+// output element is written once, with no atomics.
 #include "mer_internal.h"
-#include "mer_tiletri.h"
 
 namespace mer {
 
@@ -32,8 +30,7 @@ __device__ __forceinline__ void screen_beta(const Snap& s, int px, int py, float
 }
 
 // The three vertices' tangent rows (dx, dy, dz) of snapped triangle s, from
-// the view's rows dvb; read where needed rather than staged in LDS, which
-// keeps the one-wave workgroups small enough for twice the waves per CU.
+// the view's rows dvb.
 struct TriTangent {
   float r[9];
 };
@@ -52,9 +49,7 @@ __device__ __forceinline__ TriTangent tri_tangent(const float* __restrict__ dvb,
 // Tangent (x, y, 1/z) of the fragment at pixel (px, py) of snapped triangle
 // s: the point with that centre's screen barycentrics moves with its
 // vertices, and 1/z_k moves by -(1/z_k)^2 dz_k.
-__device__ __forceinline__ void frag_tangent(const float* __restrict__ dvb, const Snap& s, int px, int py,
-                                             float dr[3]) {
-  const TriTangent g = tri_tangent(dvb, s);
+__device__ __forceinline__ void frag_tangent(const TriTangent& g, const Snap& s, int px, int py, float dr[3]) {
   float beta[3];
   screen_beta(s, px, py, beta);
   dr[0] = dr[1] = dr[2] = 0.f;
@@ -66,141 +61,155 @@ __device__ __forceinline__ void frag_tangent(const float* __restrict__ dvb, cons
   }
 }
 
-// One workgroup per TS x TS tile of one view, one thread per pixel.  The
-// tile's triangles (and its border's) are snapped into LDS with their
-// vertices' tangent rows.  For each of the four neighbours whose triangle
-// differs, the pair's edge tangent dp (d_dir); then per channel
+// One workgroup per 16 x 16 tile of one view, one thread per pixel, as in the
+// backward sweep: each lane snaps its pixel's triangle once and publishes its
+// id and which neighbours' centres it holds; the first wave does so for the
+// 64 pixels around the tile.  A pair is classified from one bit of each side,
+// and the side that is on top (both at an intersection) publishes its
+// fragment's tangent, once for all its pairs; then every pixel takes the edge
+// tangents dp of its four pairs (d4) from there, and per channel
 //   dimg = interior tangent (c < C_out) + 1/2 sum_dir (I_A - I_B) d_dir
-// with A the left/upper pixel of each pair.
-// Six waves per SIMD (80 registers, a few bytes of spills) rather than the
-// five the unbounded allocation allows: the kernel waits on dependent loads
-// more than it issues.
-template <int TS>
-__global__ void __launch_bounds__(TS * TS) __attribute__((amdgpu_waves_per_eu(6))) k_jvp(const mer_view* __restrict__ views, int n_views,
-                                             const long long* __restrict__ btile_base,
-                                             const float* __restrict__ v, const int32_t* __restrict__ tri,
-                                             const int32_t* __restrict__ tri_id, const float* __restrict__ attr,
-                                             const float* __restrict__ dattr, int C_a, int append_z,
-                                             const float* __restrict__ img, int C_e, const float* __restrict__ dv,
-                                             int flags, float* __restrict__ dimg) {
-  __shared__ TileTris<TS, false> T;
-  // per grid position: bit d when the pixel's triangle holds neighbour d's
-  // centre (d: 0 left, 1 right, 2 up, 3 down); a border pixel sets only the
-  // bit toward its tile neighbour
-  __shared__ unsigned char s_cm[TileDims<TS>::G * TileDims<TS>::G];
-  const long long n_tiles = btile_base ? btile_base[n_views]
-                                       : (long long)((views[0].W + TS - 1) / TS) * ((views[0].H + TS - 1) / TS);
-  if ((long long)blockIdx.x >= n_tiles) return;  // the grid may hold spare workgroups
-  const long long tile = xcd_tile(blockIdx.x, n_tiles);
+// with A the left/upper pixel of each pair.  Only intersections snap the
+// neighbour's triangle, for its plane's slope.
+//
+// Bound by vector issue: building a table of the tile's distinct triangles in
+// LDS first (a hash, then one snap each) and evaluating a pair's tangent on
+// both its sides took 795 instructions per wave and 1.28 ms on 128 scenes (54
+// M px, 3 channels); this takes JVP_NOW.
+constexpr int kJq = 256 + 64;  // tile pixels, then 16 around it per side: left, right, up, down
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_jvp(
+    const mer_view* __restrict__ views, int n_views, const long long* __restrict__ btile_base,
+    const float* __restrict__ v, const int32_t* __restrict__ tri, const int32_t* __restrict__ tri_id,
+    const float* __restrict__ attr, const float* __restrict__ dattr, int C_a, int append_z,
+    const float* __restrict__ img, int C_e, const float* __restrict__ dv, int flags, float* __restrict__ dimg) {
+  __shared__ int s_t[kJq];             // triangle, -1 background, outside the view or one that does not snap
+  __shared__ unsigned char s_cm[kJq];  // bit d: that triangle holds the centre of neighbour d (0 left, 1 right, 2 up, 3 down)
+  __shared__ float s_dr[3][kJq];       // fragment tangents (x, y, 1/z) of the pixels that are on top of some pair
+  const long long tile = xcd_tile(blockIdx.x, gridDim.x);
   long long local_tile;
   const int vi = tile_view(btile_base, n_views, tile, local_tile);
   const mer_view vw = views[vi];
-  const int tiles_x = (vw.W + TS - 1) / TS;
   int x0, y0;
-  grid_xy(local_tile, tiles_x, x0, y0);
-  x0 *= TS;
-  y0 *= TS;
-  tile_tris_build<TS, false>(T, vw, x0, y0, tri_id, tri, v, nullptr);
+  grid_xy(local_tile, (vw.W + 15) >> 4, x0, y0);
+  x0 *= 16;
+  y0 *= 16;
   const float* dvb = dv ? dv + vw.v_off * 3 : nullptr;
-
-  const int lx = threadIdx.x % TS, ly = threadIdx.x / TS;
+  const int lt = threadIdx.x, lx = lt & 15, ly = lt >> 4;
   const int px = x0 + lx, py = y0 + ly;
-  const int t = tile_rec<TS>(T, lx, ly);  // record index, -1 background or outside the view
+  const bool inside = px < vw.W && py < vw.H;
+  const long long p = vw.px_off + (long long)py * vw.W + px;
+  const bool want_edge = dv && !(flags & MER_SKIP_EDGE);
+  const bool no_isect = (flags & MER_NO_INTERSECT) != 0;
+
+  // a pixel around the tile (lanes of the first wave): its place, and the
+  // tile pixel next to it
+  const int side = (lt & 63) >> 4, ri = lt & 15;
+  const int ix = side == 0 ? 0 : side == 1 ? 15 : ri, iy = side == 2 ? 0 : side == 3 ? 15 : ri;
+  const int qx = x0 + (side == 0 ? -1 : side == 1 ? 16 : ri), qy = y0 + (side == 2 ? -1 : side == 3 ? 16 : ri);
+  if (want_edge && lt < 64) {
+    int rt = -1;
+    if (qx >= 0 && qy >= 0 && qx < vw.W && qy < vw.H) rt = tri_id[vw.px_off + (long long)qy * vw.W + qx];
+    if (rt >= vw.n_t) rt = -1;
+    unsigned rc = 0;
+    if (rt >= 0) {
+      const Snap R = snap_triangle<false>(v, vw, tri_row(tri, vw, rt));
+      if (!R.ok) rt = -1;
+      else if (contains(R, x0 + ix, y0 + iy)) rc = 1u << (side ^ 1);
+    }
+    s_t[256 + lt] = rt;
+    s_cm[256 + lt] = (unsigned char)rc;
+  }
+  int t = inside ? tri_id[p] : -1;
+  if (t >= vw.n_t || t < 0) t = -1;
   Snap S;
   S.ok = false;
-  if (t >= 0) S = tile_snap(T, t);
-  const bool want_edge = dv && !(flags & MER_SKIP_EDGE);
-  if (want_edge) {
-    s_cm[tt_pos<TS>(lx, ly)] = t >= 0 ? (unsigned char)cover_mask(S, px, py) : (unsigned char)0;
-    if (threadIdx.x < 4 * TS) {  // the border, in tile_tris_build's order: top, bottom, left, right
-      const int side = threadIdx.x / TS, j = threadIdx.x % TS;
-      const int bx = side < 2 ? j : side == 2 ? -1 : TS, by = side == 0 ? -1 : side == 1 ? TS : j;
-      const int ix = side < 2 ? j : side == 2 ? 0 : TS - 1, iy = side == 0 ? 0 : side == 1 ? TS - 1 : j;
-      const int back = side == 0 ? 3 : side == 1 ? 2 : side == 2 ? 1 : 0;  // from the border pixel to the tile
-      const int tb = tile_rec<TS>(T, bx, by);
-      s_cm[tt_pos<TS>(bx, by)] =
-          tb >= 0 && contains(tile_snap(T, tb), x0 + ix, y0 + iy) ? (unsigned char)(1u << back) : (unsigned char)0;
-    }
-    __syncthreads();
-  }
-  if (px >= vw.W || py >= vw.H) return;
-  const long long p = vw.px_off + (long long)py * vw.W + px;
+  if (t >= 0) S = snap_triangle<false>(v, vw, tri_row(tri, vw, t));
+  if (!S.ok) t = -1;
+  TriTangent gt;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) gt.r[i] = 0.f;
+  if (dv && t >= 0) gt = tri_tangent(dvb, S);
 
   // ---- micro-edge term: tangent of the edge position of each differing pair
   float d4[4] = {0.f, 0.f, 0.f, 0.f};  // left, right, up, down
   if (want_edge) {
-    // A pair of two covered pixels has a term only when one side's
-    // triangle holds the other's centre (else the triangles merely touch),
-    // and under NO_INTERSECT only when exactly one does: such pairs leave
-    // pend before any triangle is read.
-    const unsigned cm = s_cm[tt_pos<TS>(lx, ly)];
-    unsigned pend = 0, held = 0;  // held bit d: neighbour d's triangle holds this centre
-    int tn4[4];
+    const unsigned cm = t >= 0 ? cover_mask(S, px, py) : 0u;
+    s_t[lt] = t;
+    s_cm[lt] = (unsigned char)cm;
+    __syncthreads();
+    // the place of neighbour d
+    auto nq = [&](int d) -> int {
+      if (d == 0) return lx > 0 ? lt - 1 : 256 + ly;
+      if (d == 1) return lx < 15 ? lt + 1 : 256 + 16 + ly;
+      if (d == 2) return ly > 0 ? lt - 16 : 256 + 32 + lx;
+      return ly < 15 ? lt + 16 : 256 + 48 + lx;
+    };
+    // One side background: the other is on top.  Both covered: the side whose
+    // centre the other triangle holds too, both sides at an intersection;
+    // triangles that merely touch have no term.
+    auto on_top = [&](int ta, int tb, bool a_holds, bool b_holds) -> bool {  // a of the pair (a, b)
+      return (ta >= 0) & (ta != tb) & ((tb < 0) | (b_holds & !(a_holds & no_isect)));
+    };
+    unsigned self = 0u, other = 0u;  // bit d: this pixel, its neighbour d is on top of their pair
+    const bool in_view[4] = {px > 0, px + 1 < vw.W, py > 0, py + 1 < vw.H};
 #pragma unroll
-    for (int dir = 0; dir < 4; ++dir) {
-      const int nx = lx + (dir == 0 ? -1 : dir == 1 ? 1 : 0);
-      const int ny = ly + (dir == 2 ? -1 : dir == 3 ? 1 : 0);
-      tn4[dir] = tile_rec<TS>(T, nx, ny);  // -1 outside the view too
-      const bool inside = px + (nx - lx) >= 0 && px + (nx - lx) < vw.W && py + (ny - ly) >= 0 && py + (ny - ly) < vw.H;
-      const unsigned cS = (s_cm[tt_pos<TS>(nx, ny)] >> (dir ^ 1)) & 1u, cN = (cm >> dir) & 1u;
-      held |= cS << dir;
-      const bool both = t >= 0 && tn4[dir] >= 0;
-      const bool term = !both || (cS | cN) && !((flags & MER_NO_INTERSECT) && (cS & cN));
-      if (inside && tn4[dir] != t && term) pend |= 1u << dir;
+    for (int d = 0; d < 4; ++d) {
+      const int q = nq(d), tn = s_t[q];
+      const bool mine = (cm >> d) & 1u, theirs = (s_cm[q] >> (d ^ 1)) & 1u, in = inside & in_view[d];
+      self |= in & on_top(t, tn, mine, theirs) ? 1u << d : 0u;
+      other |= in & on_top(tn, t, theirs, mine) ? 1u << d : 0u;
     }
-    float drs[3] = {0.f, 0.f, 0.f};  // this pixel's own fragment tangent
-    if (t >= 0 && pend) frag_tangent(dvb, S, px, py, drs);
-#pragma unroll 1
-    while (__ballot(pend != 0)) {
-      if (pend == 0) continue;
-      const int dir = __builtin_ctz(pend);
-      pend &= pend - 1;
-      const int tn = dir == 0 ? tn4[0] : dir == 1 ? tn4[1] : dir == 2 ? tn4[2] : tn4[3];
-      const int nx = px + (dir == 0 ? -1 : dir == 1 ? 1 : 0);
-      const int ny = py + (dir == 2 ? -1 : dir == 3 ? 1 : 0);
-      const bool selfA = dir == 1 || dir == 3;  // this pixel has the smaller coordinate
-      const int axis = dir < 2 ? 0 : 1;
-      float dp;
-      if (tn < 0) {
-        dp = drs[axis];  // overhang over background: this (covered) side is on top
-      } else {
-        const Snap Sn = tile_snap(T, tn);
-        if (t < 0) {
-          float drn[3];
-          frag_tangent(dvb, Sn, nx, ny, drn);
-          dp = drn[axis];
-        } else {
-          const bool cS = (held >> dir) & 1u;  // the neighbour's triangle holds this centre
-          const bool cN = (cm >> dir) & 1u;    // this triangle holds the neighbour's centre
-          if (cS != cN) {
-            if (cS) {
-              dp = drs[axis];
-            } else {
-              float drn[3];
-              frag_tangent(dvb, Sn, nx, ny, drn);
-              dp = drn[axis];
-            }
-          } else {
-            // A = left/upper pixel.  dp = (-sA drA_axis + drA_q + sB drB_axis - drB_q) / (sB - sA)
-            const float s_self = plane_slope(S, axis), s_n = plane_slope(Sn, axis);
-            const float sA = selfA ? s_self : s_n, sB = selfA ? s_n : s_self;
-            const float dlt = sB - sA;
-            if (!(dlt > 0.f) || !isfinite(dlt)) continue;
-            float drn[3];
-            frag_tangent(dvb, Sn, nx, ny, drn);
-            const float* drA = selfA ? drs : drn;
-            const float* drB = selfA ? drn : drs;
-            const float num = ((-sA) * drA[axis] + drA[2]) + (sB * drB[axis] - drB[2]);
-            dp = num / dlt;
-          }
-        }
+    if (self) {
+      float dr[3];
+      frag_tangent(gt, S, px, py, dr);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s_dr[k][lt] = dr[k];
+    }
+    if (lt < 64) {
+      const int rt = s_t[256 + lt], it = iy * 16 + ix, ti = s_t[it];
+      const bool r_holds = (s_cm[256 + lt] >> (side ^ 1)) & 1u, i_holds = (s_cm[it] >> side) & 1u;
+      if (x0 + ix < vw.W && y0 + iy < vw.H && on_top(rt, ti, r_holds, i_holds)) {
+        const Snap R = snap_triangle<false>(v, vw, tri_row(tri, vw, rt));
+        float dr[3];
+        frag_tangent(tri_tangent(dvb, R), R, qx, qy, dr);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s_dr[k][256 + lt] = dr[k];
       }
-      if (dir == 0) d4[0] = dp;
-      else if (dir == 1) d4[1] = dp;
-      else if (dir == 2) d4[2] = dp;
+    }
+    __syncthreads();  // the tangents are published
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const int axis = d >> 1;
+      const unsigned both = (self & other) >> d & 1u;
+      if (!both && ((self | other) >> d & 1u)) d4[d] = s_dr[axis][(self >> d & 1u) ? lt : nq(d)];
+    }
+    unsigned isect = self & other;
+#pragma unroll 1
+    while (isect) {
+      const int d = __builtin_ctz(isect);
+      isect &= isect - 1;
+      const int q = nq(d), axis = d >> 1;
+      const bool selfA = d & 1;  // this pixel has the smaller coordinate
+      // dp = (-sA drA_axis + drA_q + sB drB_axis - drB_q) / (sB - sA), A the left/upper pixel
+      const Snap Sn = snap_triangle<false>(v, vw, tri_row(tri, vw, s_t[q]));
+      Snap So = S;
+      asm volatile("" : "+v"(So.z[0]), "+v"(So.z[1]), "+v"(So.z[2]), "+v"(So.X[0]), "+v"(So.X[1]), "+v"(So.X[2]),
+                   "+v"(So.Y[0]), "+v"(So.Y[1]), "+v"(So.Y[2]), "+v"(So.D));  // the slope stays in this rare branch
+      const float s_self = plane_slope(So, axis), s_n = plane_slope(Sn, axis);
+      const float sA = selfA ? s_self : s_n, sB = selfA ? s_n : s_self;
+      const float dlt = sB - sA;
+      if (!(dlt > 0.f) || !isfinite(dlt)) continue;
+      const int qA = selfA ? lt : q, qB = selfA ? q : lt;
+      const float num = ((-sA) * s_dr[axis][qA] + s_dr[2][qA]) + (sB * s_dr[axis][qB] - s_dr[2][qB]);
+      const float dp = num / dlt;
+      if (d == 0) d4[0] = dp;
+      else if (d == 1) d4[1] = dp;
+      else if (d == 2) d4[2] = dp;
       else d4[3] = dp;
     }
   }
+  if (!inside) return;
 
   // ---- interior: forward derivative of sum_k b_k a_kc at the fixed index
   float db[3] = {0.f, 0.f, 0.f}, b[3] = {0.f, 0.f, 0.f};
@@ -213,7 +222,6 @@ __global__ void __launch_bounds__(TS * TS) __attribute__((amdgpu_waves_per_eu(6)
     if (dv) {
       // the material point at this centre moves by delta = sum_j beta_j dv_j,
       // so beta_i changes by -grad_P beta_i . delta
-      const TriTangent gt = tri_tangent(dvb, S);
       float ex = 0.f, ey = 0.f;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
@@ -326,19 +334,16 @@ __global__ void __launch_bounds__(TS * TS) __attribute__((amdgpu_waves_per_eu(6)
 int launch_jvp(const mer_plan* P, const mer_view* views, const float* v, const int32_t* tri, const int32_t* tri_id,
                const float* attr, const float* dattr, int C_a, int append_z, const float* img, int C_e,
                const float* dv, int flags, float* dimg, void* ws, hipStream_t st) {
+  // 16x16 tile prefix per view (one view needs none); the rasterizer's status
+  // words are left alone
   long long* tab = (long long*)((char*)ws + P->off_bviewtab);
-  // 8x8 tile prefix per view (one wave per tile); the rasterizer's status
-  // words are left alone.  A view has at most 4 times as many of these tiles
-  // as 16x16 ones, so 4 workgroups per 16x16 tile cover them all.
-  constexpr int TS = 8, lg = 3;
   const long long* base = P->n_views > 1 ? tab + (P->n_views + 1) : nullptr;
   if (base)
-    hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, lg, lg, tab, tab + (P->n_views + 1),
+    hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, 4, 4, tab, tab + (P->n_views + 1),
                        (long long*)nullptr);
-  const long long grid = P->total_btiles * (16 / TS) * (16 / TS);
-  if (grid > 0)
-    hipLaunchKernelGGL(k_jvp<TS>, dim3((unsigned)grid), dim3(TS * TS), 0, st, views, P->n_views,
-                       base, v, tri, tri_id, attr, dattr, C_a, append_z, img, C_e, dv, flags, dimg);
+  if (P->total_btiles > 0)
+    hipLaunchKernelGGL(k_jvp, dim3((unsigned)P->total_btiles), dim3(256), 0, st, views, P->n_views, base, v, tri, tri_id,
+                       attr, dattr, C_a, append_z, img, C_e, dv, flags, dimg);
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }
 
