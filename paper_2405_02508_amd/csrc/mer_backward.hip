@@ -243,7 +243,7 @@ __device__ __forceinline__ int slot_of(int* s_key, int* s_list, int* s_nocc, int
 // loss_part[tile].  Its rows are read first, four channels a load, while the
 // index image is on its way; one load per channel after the sweep, when most
 // rows have left the cache, took longer than the sweep (64 head views, 8
-// channels: 1.96 ms before, 1.00 now; reading both images alone takes 0.6).
+// channels: 1.96 ms before, 1.00 then; reading both images alone takes 0.6).
 // WIDE: more attribute channels than the table takes at once; its loop keeps
 // more registers live, so it gets five waves per SIMD instead of seven.
 template <bool L2, bool LOSS, bool WIDE>
@@ -266,13 +266,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ?
   __shared__ int s_t[kQ];
   __shared__ unsigned char s_cm[kQ];
   __shared__ float s_loss[4];
-  // the table starts empty and zero: a run end may raise a slot's maximum as
-  // soon as another lane has claimed the slot
-  for (int i = threadIdx.x; i < kSlots; i += blockDim.x) s_key[i] = -1;
-  for (int i = threadIdx.x; i < kSlots * kNV / 4; i += blockDim.x) reinterpret_cast<int4*>(s_acc)[i] = make_int4(0, 0, 0, 0);
-  for (int i = threadIdx.x; i < kSlots * 3 / 4; i += blockDim.x) reinterpret_cast<uint4*>(s_mx)[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (threadIdx.x == 0) s_nocc = 0;
-
   const long long tile = xcd_tile(blockIdx.x, gridDim.x);
   long long local_tile;
   const int vi = tile_view(btile_base, n_views, tile, local_tile);
@@ -297,6 +290,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ?
   const bool v2tar = L2 && (C_e & 1) == 0 && ((uintptr_t)target & 7) == 0;
   const bool v2g = !L2 && (ld_g & 1) == 0 && ((uintptr_t)g & 7) == 0;
 
+  // the ring, by the first wave: each lane one ring pixel; (ix, iy) is the
+  // tile pixel next to it
+  const int side = (lt & 63) >> 4, ri = lt & 15;
+  const int ix = side == 0 ? x0 : side == 1 ? x0 + 15 : x0 + ri;
+  const int iy = side == 2 ? y0 : side == 3 ? y0 + 15 : y0 + ri;
+  int t = -1, rt = -1;
+  if (inside) t = tri_id[p];
+  if (want_edge && lt < 64) {
+    const int qx = side == 0 ? x0 - 1 : side == 1 ? x0 + 16 : ix;
+    const int qy = side == 2 ? y0 - 1 : side == 3 ? y0 + 16 : iy;
+    if (qx >= 0 && qy >= 0 && qx < vw.W && qy < vw.H) rt = tri_id[vw.px_off + (long long)qy * vw.W + qx];
+  }
+  if (t >= vw.n_t || t < 0) t = -1;
+  if (rt >= vw.n_t || rt < 0) rt = -1;
   if constexpr (LOSS) {
     float e2 = 0.f;
     if (inside)
@@ -314,32 +321,32 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ?
     if (lane == 63) s_loss[threadIdx.x >> 6] = e2;
   }
 
-  // ---- the ring, by the first wave: each lane one ring pixel.  Its id, and
-  // whether its triangle holds the centre of its neighbour in the tile (as
-  // the bit that neighbour looks up: the direction back from the ring pixel)
-  if (want_edge && threadIdx.x < 64) {
-    const int r = threadIdx.x, side = r >> 4, i = r & 15;
-    const int ix = side == 0 ? x0 : side == 1 ? x0 + 15 : x0 + i;  // the tile pixel next to it
-    const int iy = side == 2 ? y0 : side == 3 ? y0 + 15 : y0 + i;
-    const int qx = side == 0 ? x0 - 1 : side == 1 ? x0 + 16 : ix;
-    const int qy = side == 2 ? y0 - 1 : side == 3 ? y0 + 16 : iy;
-    const bool rin = qx >= 0 && qy >= 0 && qx < vw.W && qy < vw.H;
-    int rt = -1;
-    if (rin) {
-      rt = tri_id[vw.px_off + (long long)qy * vw.W + qx];
-      if (rt >= vw.n_t || rt < 0) rt = -1;
-    }
-    unsigned rc = 0;
-    if (rt >= 0 && contains(snap_triangle<false>(v, vw, tri_row(tri, vw, rt)), ix, iy)) rc = 1u << (side ^ 1);
-    s_t[256 + r] = rt;
-    s_cm[256 + r] = (unsigned char)rc;
+  // a background pixel receives nothing: a tile of them is done, before the
+  // table is cleared (64 head views, three tiles in four: 0.99 -> 0.91 ms; 256
+  // scenes, two in five: 2.20 -> 2.10; 16 views 0.181 -> 0.166)
+  if (!__syncthreads_or(t >= 0)) {
+    if constexpr (LOSS)
+      if (lt == 0) loss_part[tile] = w_l2 * ((s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]));
+    return;
   }
 
-  int t = -1;
-  if (inside) {
-    t = tri_id[p];
-    if (t >= vw.n_t || t < 0) t = -1;
+  // the table starts empty and zero: a run end may raise a slot's maximum as
+  // soon as another lane has claimed the slot
+  for (int i = threadIdx.x; i < kSlots; i += blockDim.x) s_key[i] = -1;
+  for (int i = threadIdx.x; i < kSlots * kNV / 4; i += blockDim.x) reinterpret_cast<int4*>(s_acc)[i] = make_int4(0, 0, 0, 0);
+  for (int i = threadIdx.x; i < kSlots * 3 / 4; i += blockDim.x) reinterpret_cast<uint4*>(s_mx)[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (threadIdx.x == 0) s_nocc = 0;
+
+  // the ring pixel: whether its triangle holds the centre of its neighbour in
+  // the tile (as the bit that neighbour looks up: the direction back from the
+  // ring pixel)
+  if (want_edge && lt < 64) {
+    unsigned rc = 0;
+    if (rt >= 0 && contains(snap_triangle<false>(v, vw, tri_row(tri, vw, rt)), ix, iy)) rc = 1u << (side ^ 1);
+    s_t[256 + lt] = rt;
+    s_cm[256 + lt] = (unsigned char)rc;
   }
+
   // the id as the neighbours see it (a triangle that does not snap is still
   // a triangle to them, one that holds no centre); -1 below if it does not
   const int t_id = t;
