@@ -172,6 +172,14 @@ int mer_rasterize_interpolate(const mer_plan *plan, const mer_view *views_dev, c
                               int32_t *tri_id, float *depth, float *bary, const float *attr, int C_a, int append_z,
                               float *out, void *ws, void *stream);
 
+/* mer_rasterize_interpolate that writes the whole image the edge gradients
+ * are taken on: with mask, one more channel after the attributes and z, 1
+ * where a triangle is visible and 0 on background.
+ *   out: float [total_px, C_a + append_z + mask]; C_a + append_z <= 64. */
+int mer_rasterize_image(const mer_plan *plan, const mer_view *views_dev, const float *v, const int32_t *tri,
+                        int32_t *tri_id, float *depth, float *bary, const float *attr, int C_a, int append_z,
+                        int mask, float *out, void *ws, void *stream);
+
 /* Interpolation module (supplement, "Interpolation module"):
  * out[p, c] = sum_k b_k attr[a_off + tri[t][k], c] for c < C_a and, if
  * append_z, out[p, C_a] = sum_k b_k z_k (screen z of the view's vertices);

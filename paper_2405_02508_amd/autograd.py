@@ -168,15 +168,11 @@ class RenderStep(torch.autograd.Function):
         tid = torch.empty(r.n_px, dtype=torch.int32, device=dev)
         depth = torch.empty(r.n_px, dtype=torch.float32, device=dev)
         bary = torch.empty(r.n_px, 2, dtype=torch.float32, device=dev) if r.store_bary else None
-        C = attr.shape[1] + int(r.append_z)
-        C_e = C + int(r.mask_channel)
+        C_e = attr.shape[1] + int(r.append_z) + int(r.mask_channel)
         img = torch.empty(r.n_px, C_e, dtype=torch.float32, device=dev)
-        # one pass: rasterize, resolve and interpolate
-        out = img if C_e == C else torch.empty(r.n_px, C, dtype=torch.float32, device=dev)
-        r.ctx.rasterize_interpolate(vd, r.tri, tid, ad, out, depth=depth, bary=bary, append_z=r.append_z)
-        if C_e != C:
-            img[:, :C].copy_(out)
-            img[:, C].copy_(tid >= 0)
+        # one pass: rasterize, resolve, interpolate and the mask
+        r.ctx.rasterize_interpolate(vd, r.tri, tid, ad, img, depth=depth, bary=bary, append_z=r.append_z,
+                                    mask=r.mask_channel)
         ctx.save_for_backward(vd, ad, tid, img)
         ctx.r = r
         ctx.flags = flags

@@ -452,7 +452,7 @@ __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))
                                                    const int32_t* __restrict__ tri, int32_t* __restrict__ tri_id,
                                                    float* __restrict__ depth, float* __restrict__ bary,
                                                    long long* __restrict__ status, const float* __restrict__ attr,
-                                                   int C_a, int append_z, float* __restrict__ out) {
+                                                   int C_a, int tail, float* __restrict__ out) {
   constexpr int NT = TW * TH;
   __shared__ TileRec s_tr[NT];
   // single-wave tiles: the chunk's records go to s_tr nearest first.  The
@@ -687,16 +687,16 @@ __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))
       bary[2 * p + 1] = b1;
     }
     if (out)
-      resolve_attr({v, tri, tri_id, depth, bary, attr, C_a, append_z, out}, vw, p, t, b0, b1,
+      resolve_attr({v, tri, tri_id, depth, bary, attr, C_a, tail, out}, vw, p, t, b0, b1,
                    tri_row(tri, vw, max(t, 0)));
   }
 }
 
 // --------------------------------------------------------------- launch
 int launch_rasterize(const mer_plan* P, const mer_view* views, const float* v, const int32_t* tri, int32_t* tri_id,
-                     float* depth, float* bary, const float* attr, int C_a, int append_z, float* out, void* ws,
+                     float* depth, float* bary, const float* attr, int C_a, int tail, float* out, void* ws,
                      hipStream_t st) {
-  if (P->small_px > 0) return launch_coarse(P, views, {v, tri, tri_id, depth, bary, attr, C_a, append_z, out}, ws, st);
+  if (P->small_px > 0) return launch_coarse(P, views, {v, tri, tri_id, depth, bary, attr, C_a, tail, out}, ws, st);
   char* w = (char*)ws;
   long long* viewtab = (long long*)(w + P->off_viewtab);
   long long* tri_base = viewtab;
@@ -746,11 +746,11 @@ int launch_rasterize(const mer_plan* P, const mer_view* views, const float* v, c
     if (bary)                                                                                            \
       hipLaunchKernelGGL((k_raster<TW, TH, true>), dim3((unsigned)nt), dim3(TW * TH), 0, st, views,      \
                          P->n_views, tri_base, tile_base, rec, bbox, offs, bins, count, P->bin_cap, v,   \
-                         tri, tri_id, depth, bary, status, attr, C_a, append_z, out);                    \
+                         tri, tri_id, depth, bary, status, attr, C_a, tail, out);                    \
     else                                                                                                 \
       hipLaunchKernelGGL((k_raster<TW, TH, false>), dim3((unsigned)nt), dim3(TW * TH), 0, st, views,     \
                          P->n_views, tri_base, tile_base, rec, bbox, offs, bins, count, P->bin_cap, v,   \
-                         tri, tri_id, depth, bary, status, attr, C_a, append_z, out);                    \
+                         tri, tri_id, depth, bary, status, attr, C_a, tail, out);                    \
   } while (0)
   if (P->tile_w == 8 && P->tile_h == 8) MER_RASTER(8, 8);
   else if (P->tile_w == 16 && P->tile_h == 16) MER_RASTER(16, 16);

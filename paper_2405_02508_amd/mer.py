@@ -21,6 +21,7 @@ SKIP_EDGE = 2
 SKIP_INTERP = 4
 
 SYMBOLS = ("mer_plan_init", "mer_transform", "mer_transform_bwd", "mer_rasterize", "mer_rasterize_interpolate",
+           "mer_rasterize_image",
            "mer_interpolate", "mer_backface", "mer_edge_grad", "mer_interpolate_bwd", "mer_backward_fused",
            "mer_backward_l2", "mer_backward_l2_noalloc", "mer_jvp", "mer_texture", "mer_texture_bwd", "mer_status",
            "mer_strerror", "mer_version")
@@ -77,6 +78,7 @@ def lib():
         L.mer_plan_init.argtypes = [ctypes.POINTER(View), i, ctypes.POINTER(Tuning), ctypes.POINTER(Plan)]
         L.mer_rasterize.argtypes = [ctypes.POINTER(Plan), P, P, P, P, P, P, P, P]
         L.mer_rasterize_interpolate.argtypes = [ctypes.POINTER(Plan), P, P, P, P, P, P, P, i, i, P, P, P]
+        L.mer_rasterize_image.argtypes = [ctypes.POINTER(Plan), P, P, P, P, P, P, P, i, i, i, P, P, P]
         L.mer_interpolate.argtypes = [ctypes.POINTER(Plan), P, P, i, P, P, P, P, i, P, P]
         L.mer_backface.argtypes = [ctypes.POINTER(Plan), P, P, P, P, P, P]
         L.mer_transform.argtypes = [ctypes.POINTER(Plan), P, P, P, P, P, P]
@@ -220,8 +222,10 @@ class Context:
                                      _ptr(v), _ptr(tri), _ptr(tri_id), _ptr(bary), int(bool(append_z)), _ptr(out),
                                      _stream()))
 
-    def rasterize_interpolate(self, v, tri, tri_id, attr, out, depth=None, bary=None, append_z=False):
-        """rasterize + interpolate in one pass (out bit-identical to the two calls)."""
+    def rasterize_interpolate(self, v, tri, tri_id, attr, out, depth=None, bary=None, append_z=False,
+                              mask=False):
+        """rasterize + interpolate in one pass (out bit-identical to the two
+        calls); with ``mask`` out has one more channel, 1 where covered."""
         _need(tri_id, _i32, "tri_id")
         _need(attr, _f32, "attr")
         _need(out, _f32, "out")
@@ -233,10 +237,10 @@ class Context:
         self._px(tri_id, "tri_id")
         self._px(depth, "depth")
         self._px(bary, "bary", 2)
-        self._px(out, "out", int(attr.shape[1]) + int(bool(append_z)))
-        _check(lib().mer_rasterize_interpolate(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri),
-                                               _ptr(tri_id), _ptr(depth), _ptr(bary), _ptr(attr), int(attr.shape[1]),
-                                               int(bool(append_z)), _ptr(out), _ptr(self.ws), _stream()))
+        self._px(out, "out", int(attr.shape[1]) + int(bool(append_z)) + int(bool(mask)))
+        _check(lib().mer_rasterize_image(self.plan, _ptr(self.views_dev), _ptr(v), _ptr(tri), _ptr(tri_id),
+                                         _ptr(depth), _ptr(bary), _ptr(attr), int(attr.shape[1]),
+                                         int(bool(append_z)), int(bool(mask)), _ptr(out), _ptr(self.ws), _stream()))
 
     # vertex transform ---------------------------------------------------
     def transform(self, cams, v_world, v_screen):
