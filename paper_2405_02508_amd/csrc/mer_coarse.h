@@ -400,6 +400,14 @@ __device__ __forceinline__ int dot2(int a, int b, int c) {
 }
 __device__ __forceinline__ int pack2(int x, int y) { return (x & 0xffff) | (int)((unsigned)y << 16); }
 
+// The wave's LDS accesses before this are done before those after it; lanes of
+// one wave only.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Candidate record, 64 bytes.  "Tight" triangles span less than 128 px
 // along each axis (|A|, |B| < 2^15) and their vertex 1/z lie in [2^-64, 2^64].
 // At a centre inside the triangle's box an edge value is twice the area of a
@@ -420,6 +428,7 @@ struct CandRec {
 };
 
 constexpr int kSmallPx = 40;  // a box of at most this many centres can be rasterized by the candidate's own lane
+constexpr int kStageC = 16;  // channels of a row staged in the records' memory: 64 a wave
 constexpr int kMaskSlot = 20;  // from this bit on: the record's place
 constexpr int kMaskGen = 16;  // bit of the candidate's tile mask: general record; the three above it: tl
 
@@ -433,7 +442,8 @@ constexpr int kMaskGen = 16;  // bit of the candidate's tile mask: general recor
 // candidate is skipped once no pixel's surface is as far as its bound.
 // direct: no lists; the plan's one view has few triangles and every tile
 // scans them all.
-template <int CTL, int NT>
+// STAGED: the resolve writes its image rows by way of LDS (below).
+template <int CTL, int NT, bool STAGED>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_craster(const mer_view* __restrict__ views, const CTile* __restrict__ tiles,
                                                  const int2* __restrict__ count, const int* __restrict__ bins,
                                                  const long long* __restrict__ tri_base, int direct, ResolveOut R,
@@ -442,6 +452,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
   constexpr int kChunk = NT;  // candidates taken at a time
   __shared__ unsigned long long s_key[NPX];
   __shared__ CRec s_rec[kChunk];
+  static_assert(sizeof(CRec) * kChunk >= sizeof(float) * 64 * kStageC * NW, "a wave's staged rows fit the records");
   __shared__ unsigned s_mask[kChunk];
   __shared__ float s_qb[kChunk];
   __shared__ int s_hist[64];
@@ -786,35 +797,59 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
   }
   __syncthreads();
   if (direct && g == 0 && tid < 8) status[tid] = tid == 1 ? (long long)(n_items > 0 ? s_culled : 0) : 0;
-  // ---- resolve, a row of the tile at a time
+  // ---- resolve, a row of the tile at a time.  STAGED: the image rows go
+  // through the wave's part of the records' memory, and the wave writes them as
+  // spans of consecutive floats.
+  const int C = out_channels(R);
+  float* stage = reinterpret_cast<float*>(s_rec) + wv * 64 * kStageC;
 #pragma unroll 1
   for (int i = tid; i < NPX; i += NT) {
     const int x = i & (CT - 1), y = i >> CTL;
     const int px = x0 + x, py = y0 + y;
-    if (px >= vw.W || py >= vw.H) continue;
-    const unsigned long long best = n_items > 0 ? s_key[key_at(x, y)] : 0ull;
-    const int t = key_tri(best);
-    const long long p = vw.px_off + (long long)py * vw.W + px;
-    R.tri_id[p] = t;
-    if (R.depth) R.depth[p] = t >= 0 ? rcp_rn(key_q(best)) : 0.0f;
-    if (R.bary || R.out) {
-      float b0 = 0.f, b1 = 0.f;
-      int idx[3] = {0, 0, 0};
-      if (t >= 0) {
-        const int32_t* r = tri_row(R.tri, vw, t);
+    const bool inside = px < vw.W && py < vw.H;
+    if constexpr (!STAGED)
+      if (!inside) continue;
+    if (!STAGED || inside) {
+      const unsigned long long best = n_items > 0 ? s_key[key_at(x, y)] : 0ull;
+      const int t = key_tri(best);
+      const long long p = vw.px_off + (long long)py * vw.W + px;
+      R.tri_id[p] = t;
+      if (R.depth) R.depth[p] = t >= 0 ? rcp_rn(key_q(best)) : 0.0f;
+      if (R.bary || R.out) {
+        float b0 = 0.f, b1 = 0.f;
+        int idx[3] = {0, 0, 0};
+        if (t >= 0) {
+          const int32_t* r = tri_row(R.tri, vw, t);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) idx[k] = r[k];
-        float wa, wb, wn;
-        resolve_products(snap_visible(R.v, vw, idx), px, py, wa, wb, wn);
-        const float rr = __builtin_amdgcn_rcpf(wn);
-        b0 = wa * rr;
-        b1 = wb * rr;
+          for (int k = 0; k < 3; ++k) idx[k] = r[k];
+          float wa, wb, wn;
+          resolve_products(snap_visible(R.v, vw, idx), px, py, wa, wb, wn);
+          const float rr = __builtin_amdgcn_rcpf(wn);
+          b0 = wa * rr;
+          b1 = wb * rr;
+        }
+        if (R.bary) {
+          R.bary[2 * p] = b0;
+          R.bary[2 * p + 1] = b1;
+        }
+        if constexpr (STAGED) resolve_attr(R, vw, stage + lane * C, 0, t, b0, b1, idx);
+        else if (R.out) resolve_attr(R, vw, R.out + p * C, row_vec(C, R.out), t, b0, b1, idx);
       }
-      if (R.bary) {
-        R.bary[2 * p] = b0;
-        R.bary[2 * p + 1] = b1;
+    }
+    if constexpr (STAGED) {
+      // the wave's 64 pixels are 64 / CT rows of the tile; each row's pixels
+      // inside the view are one span of the image
+      wave_lds_fence();
+      constexpr int PW = CT < 64 ? CT : 64;
+      const int n = min(CT, vw.W - x0) * C, yb = y0 + ((i - lane) >> CTL);
+#pragma unroll 1
+      for (int k = 0; k < 64 / PW; ++k) {
+        if (yb + k >= vw.H) break;
+        float* o = R.out + (vw.px_off + (long long)(yb + k) * vw.W + x0) * C;
+        const float* sp = stage + k * PW * C;
+        for (int e = lane; e < n; e += 64) o[e] = sp[e];
       }
-      if (R.out) resolve_attr(R, vw, p, t, b0, b1, idx);
+      wave_lds_fence();
     }
   }
 }
@@ -824,6 +859,19 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
 // have at most this many chunks of candidates to look at, every tile scans
 // every triangle, in one launch instead of five.
 constexpr int kDirectChunks = 512;
+
+// Image rows that no vector store takes whole (other than 3, 4, 8, ... floats)
+// are written a float a lane, C lines a store; from some width on it is faster
+// to pass them through LDS.  k_craster, us, own rows / through LDS: 16 head
+// views of 1024 x 667 (32 x 32 tiles) 2 channels 97 / 108, 5 147 / 137, 7 206 /
+// 150, 11 435 / 198, 14 671 / 234; 4 views of 731 x 413 (16 x 16 tiles, half as
+// long spans) 5 57 / 61, 7 60 / 60, 9 68 / 60, 14 98 / 64; one 300 x 300 view
+// (8 x 8 tiles, an eighth of the chip) 9 36 / 37, 14 38 / 39.
+static bool staged_rows(const ResolveOut& R, int ctl) {
+  if (!R.out) return false;
+  const int C = out_channels(R);
+  return row_vec(C, R.out) == 0 && C <= kStageC && (ctl == 5 ? C >= 5 : ctl == 4 && C >= 9);
+}
 
 static int launch_coarse(const mer_plan* P, const mer_view* views, const ResolveOut& R, void* ws, hipStream_t st) {
   char* w = (char*)ws;
@@ -855,12 +903,15 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
                          R.v, R.tri, tri_base, tile_base, ctl, (int)P->n_bingroups, count, seg, seg_n, large, status,
                          tiles, bins);
   }
-#define MER_CRASTER(CTL, NT)                                                                                         \
-  hipLaunchKernelGGL((k_craster<CTL, NT>), dim3((unsigned)nt), dim3(NT), 0, st, views, tiles, count, bins, tri_base, \
-                     direct, R, status)
-  if (ctl == 5) MER_CRASTER(5, 256);
-  else if (ctl == 4) MER_CRASTER(4, 256);
-  else MER_CRASTER(3, 256);
+#define MER_CRASTER(CTL, ST)                                                                                          \
+  hipLaunchKernelGGL((k_craster<CTL, 256, ST>), dim3((unsigned)nt), dim3(256), 0, st, views, tiles, count, bins,      \
+                     tri_base, direct, R, status)
+  const bool staged = staged_rows(R, ctl);
+  if (ctl == 5 && staged) MER_CRASTER(5, true);
+  else if (ctl == 5) MER_CRASTER(5, false);
+  else if (ctl == 4 && staged) MER_CRASTER(4, true);
+  else if (ctl == 4) MER_CRASTER(4, false);
+  else MER_CRASTER(3, false);
 #undef MER_CRASTER
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }

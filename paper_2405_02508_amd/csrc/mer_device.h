@@ -532,7 +532,7 @@ __device__ __forceinline__ float4 row4(const float* __restrict__ a, int vec, int
   if (n > 3) x.w = a[3];
   return x;
 }
-__device__ __forceinline__ int row_vec(int C, const void* base) {
+__host__ __device__ __forceinline__ int row_vec(int C, const void* base) {
   return C == 3 ? 3 : ((C & 3) == 0 && ((uintptr_t)base & 15) == 0) ? 4 : 0;
 }
 __device__ __forceinline__ float f4(const float4& x, int j) { return j == 0 ? x.x : j == 1 ? x.y : j == 2 ? x.z : x.w; }

@@ -686,9 +686,11 @@ __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))
       bary[2 * p] = b0;
       bary[2 * p + 1] = b1;
     }
-    if (out)
-      resolve_attr({v, tri, tri_id, depth, bary, attr, C_a, tail, out}, vw, p, t, b0, b1,
-                   tri_row(tri, vw, max(t, 0)));
+    if (out) {
+      const ResolveOut R = {v, tri, tri_id, depth, bary, attr, C_a, tail, out};
+      const int C = out_channels(R);
+      resolve_attr(R, vw, out + p * C, row_vec(C, out), t, b0, b1, tri_row(tri, vw, max(t, 0)));
+    }
   }
 }
 

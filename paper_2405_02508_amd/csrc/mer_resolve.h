@@ -21,15 +21,16 @@ struct ResolveOut {
   float* __restrict__ out;
 };
 
-// Interpolated row of pixel p (triangle t with index row idx, -1 background)
+__host__ __device__ __forceinline__ int out_channels(const ResolveOut& R) { return R.C_a + (R.tail & 1) + (R.tail >> 1); }
+
+// Interpolated row of a pixel (triangle t with index row idx, -1 background)
 // with perspective barycentrics b0, b1: the arithmetic of the interpolation kernel, four
-// channels a load and a store where the channel counts allow.
-__device__ __forceinline__ void resolve_attr(const ResolveOut& R, const mer_view& vw, long long p, int t, float b0,
-                                             float b1, const int32_t* idx) {
-  const int C_a = R.C_a, C = C_a + (R.tail & 1) + (R.tail >> 1);
+// channels a load and a store where the channel counts allow.  o: where the
+// row goes, vout: the vector width of a store there.
+__device__ __forceinline__ void resolve_attr(const ResolveOut& R, const mer_view& vw, float* o, int vout, int t,
+                                             float b0, float b1, const int32_t* idx) {
+  const int C_a = R.C_a, C = out_channels(R);
   const float* attr = R.attr;
-  float* o = R.out + p * C;
-  const int vout = row_vec(C, R.out);
   const bool a_al = ((vw.a_off * C_a) & 3) == 0;
   const int va = row_vec(C_a, attr) == 3 ? 3 : row_vec(C_a, attr) == 4 && a_al ? 4 : 0;
   float b2 = 0.f, zv = 0.f;
