@@ -16,11 +16,14 @@ int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 // Log2 of the coarse tiles' side.  A workgroup takes one tile, so there have
 // to be enough of them for 256 compute units: 32 x 32 pixels from 2048 tiles
 // on, or from 1024 when they hold few triangles (short workgroups); 8 x 8
-// where even 16 x 16 leaves most of the chip idle and the lists are long.
+// where 16 x 16 gives fewer than 16 workgroups a compute unit and the lists
+// are long (a tile runs as long as its list, and the entries that triangles
+// over several small tiles add are few beside it).
 // Steps measured on both sides of the lines (us a pass, 32 / 16 pixels): 1196
 // tiles of 214 triangles 535 / 490, 1452 of 74 119 / 131, 1444 of 2 102 / 114,
 // 625 of 131 111 / 86; (16 / 8 pixels) 64 tiles of 16 x 16 with 3125
-// triangles each 90 / 69, 25 with 39 38 / 53.
+// triangles each 90 / 69, 2688 with 583 174 / 144, 25 with 39 38 / 53, 2500
+// with 33 82 / 113.
 int coarse_log2(int64_t tiles32, int64_t tiles16, int64_t tris) {
   if (tiles32 >= 2048 || (tiles32 >= 1024 && tris <= 128 * tiles32)) return 5;
   return tiles16 < 4096 && tris >= 256 * tiles16 ? 3 : 4;
