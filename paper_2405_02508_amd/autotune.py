@@ -1,5 +1,5 @@
-"""Autotuner for the rasterizer's tile shape, small-triangle limit, large-
-triangle limit and bin pool.
+"""Autotuner for the rasterizer (lists of coarse tiles, or per-tile lists with
+their tile shape and large-triangle limit) and its bin pool.
 
 None of these change the results (the visibility rule is order-independent
 and the overflow path is exact); they only change speed and workspace size.
@@ -10,7 +10,10 @@ For a view table and its geometry the tuner:
   2. times mer_rasterize for each candidate with HIP events on the current
      stream and keeps the fastest.
 Choices are cached in a JSON file keyed by a shape class (view count,
-pixel and triangle counts rounded to powers of two).
+pixel and triangle counts rounded to powers of two).  An entry names the lists
+its pool was measured for: one with small_px >= 0 that does not say "coarse" is
+from before they existed, when triangles of few pixels took no entries, and is
+measured anew (a pool too small for its lists is exact but slow).
 """
 from __future__ import annotations
 
@@ -55,7 +58,7 @@ def tune(views_i64, v, tri, device="cuda", candidates=CANDIDATES, reps=3, cache_
     key = shape_class(views_i64)
     if use_cache and cache_path:
         hit = _load(cache_path).get(key)
-        if hit:
+        if hit and (hit.get("small_px", 0) < 0 or hit.get("lists") == "coarse"):
             hit["tile"] = tuple(hit["tile"])
             hit["cached"] = True
             return hit
@@ -94,6 +97,7 @@ def tune(views_i64, v, tri, device="cuda", candidates=CANDIDATES, reps=3, cache_
     if cache_path:
         data = _load(cache_path)
         data[key] = {k: out[k] for k in ("tile", "small_px", "big_tiles", "bin_cap", "entries", "ms")}
+        data[key]["lists"] = "tile" if out["small_px"] < 0 else "coarse"
         os.makedirs(os.path.dirname(cache_path), exist_ok=True)
         tmp = cache_path + ".tmp"
         with open(tmp, "w") as f:
