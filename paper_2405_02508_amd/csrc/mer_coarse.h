@@ -315,6 +315,9 @@ __global__ void __launch_bounds__(kBinBlock) k_ccount(const mer_view* __restrict
   if (m && lane == 0) atomicAdd((unsigned long long*)status + 1, (unsigned long long)__popcll(m));
 }
 
+// Workgroups for the large triangles, whether there are any or not: 16 views of
+// few large triangles take 9 us in k_clarge and 13 in the fill (256 workgroups
+// 19 and 30), and an empty list costs the same 4 to 5 us with either.
 constexpr int kLargeGrid = 1024;
 
 __global__ void __launch_bounds__(kBinBlock) k_clarge(const mer_view* __restrict__ views, int n_views,
