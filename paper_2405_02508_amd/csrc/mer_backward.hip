@@ -270,10 +270,10 @@ __device__ __forceinline__ int slot_of(int* s_key, int* s_list, int* s_nocc, int
 // index image is on its way; one load per channel after the sweep, when most
 // rows have left the cache, took longer than the sweep (64 head views, 8
 // channels: 1.96 ms before, 1.00 then; reading both images alone takes 0.6).
-// WIDE: more attribute channels than the table takes at once; its loop keeps
-// more registers live, so it gets five waves per SIMD instead of seven.
+// WIDE: more attribute channels than the table takes at once; its loop takes
+// up to 74 registers, two more than seven waves per SIMD leave (spills).
 template <bool L2, bool LOSS, bool WIDE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 5 : 7))) k_backward(const mer_view* __restrict__ views, int n_views,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 6 : 7))) k_backward(const mer_view* __restrict__ views, int n_views,
                                                   const long long* __restrict__ btile_base,
                                                   const float* __restrict__ v, const int32_t* __restrict__ tri,
                                                   const int32_t* __restrict__ tri_id, const float* __restrict__ attr,
@@ -723,14 +723,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ?
     }
   }
   if constexpr (WIDE) {
-    // ---- channels 8 on: the table again, eight at a time, same slots.  Added
-    // to memory by each run end instead, scattered over the vertices' rows,
-    // channels 8 to 15 of four 731 x 413 views took 320 of the adjoint's
-    // 350 us; the whole adjoint takes 43 this way.
+    // ---- channels 8 on: the table again, eight at a time, same slots, in
+    // binary32 this time (LDS float adds): a fixed-point group rounds a channel
+    // by the largest of its four, and one 2^24 below it to zero.  Added to
+    // memory by each run end instead, scattered over the vertices' rows,
+    // channels 8 to 15 of four 731 x 413 views took 320 of the adjoint's 350
+    // us; the whole adjoint takes 61 this way (41 with the table's integers:
+    // an LDS float add costs more than an integer one).
+    float* acc = reinterpret_cast<float*>(s_acc);
     for (int cb = kCTab; attr_tab && cb < C_a; cb += kCTab) {
       __syncthreads();  // the last round's sums are flushed
       for (int i = threadIdx.x; i < kSlots * kNV / 4; i += blockDim.x) reinterpret_cast<int4*>(s_acc)[i] = make_int4(0, 0, 0, 0);
-      for (int i = threadIdx.x; i < kSlots * 3 / 4; i += blockDim.x) reinterpret_cast<uint4*>(s_mx)[i] = make_uint4(0u, 0u, 0u, 0u);
       __syncthreads();
       const bool two = C_a > cb + 4;
 #pragma unroll
@@ -742,36 +745,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ?
       if (emit) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          unsigned m1 = 0u, m2 = 0u;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            m1 = max(m1, __float_as_uint(sa0[4 * k + j]) & 0x7fffffffu);
-            m2 = max(m2, __float_as_uint(sa1[4 * k + j]) & 0x7fffffffu);
-          }
-          if (slot[k] < 0) continue;
-          atomicMax(&s_mx[__umul24(slot[k], 3) + 1], m1);
-          if (two) atomicMax(&s_mx[__umul24(slot[k], 3) + 2], m2);
-        }
-      }
-      __syncthreads();  // the maxima are final
-      if (emit) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-#pragma unroll
-          for (int grp = 1; grp < 3; ++grp) {
-            if (grp == 2 && !two) continue;
-            const unsigned M = slot[k] >= 0 ? s_mx[slot[k] * 3 + grp] : 0x7f800000u;
-            int E = 0;
-            (void)frexpf(__uint_as_float(M), &E);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const float x = grp == 1 ? sa0[4 * k + j] : sa1[4 * k + j];
-              const int c = cb + 4 * (grp - 1) + j;
-              if (M < 0x7f800000u)
-                atomicAdd(&s_acc[__umul24(slot[k], kNV) + 4 * grp - 1 + j], round_half_up(ldexpf(x, 22 - E)));
-              else if (x != 0.f && c < C_a)
-                atomicAdd(g_attr + (vw.a_off + S.idx[k]) * C_a + c, x);
-            }
+          for (int j = 0; j < 8; ++j) {
+            const float x = j < 4 ? sa0[4 * k + j] : sa1[4 * k + j - 4];
+            if (j >= 4 && !two) continue;
+            if (slot[k] >= 0)
+              atomicAdd(&acc[__umul24(slot[k], kNV) + j], x);  // columns past C_a hold zeros and are never flushed
+            else if (x != 0.f && cb + j < C_a)
+              atomicAdd(g_attr + (vw.a_off + S.idx[k]) * C_a + cb + j, x);
           }
         }
       }
@@ -780,11 +761,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ?
       for (int k = threadIdx.x; k < nocc * nch; k += blockDim.x) {
         const int i = k / nch, j = k - i * nch;
         const int s = s_list[i];
-        const int qv = s_acc[s * kNV + 3 + j];
-        if (qv == 0) continue;
-        int E = 0;
-        (void)frexpf(__uint_as_float(s_mx[s * 3 + (j < 4 ? 1 : 2)]), &E);
-        atomicAdd(g_attr + (vw.a_off + s_key[s]) * C_a + cb + j, ldexpf((float)qv, E - 22));
+        const float x = acc[s * kNV + j];
+        if (x != 0.f) atomicAdd(g_attr + (vw.a_off + s_key[s]) * C_a + cb + j, x);
       }
     }
   }
