@@ -101,12 +101,11 @@ typedef struct mer_plan {
   int64_t total_v, off_vbase;         /* screen vertices over all views, their per-view prefix */
   int64_t off_bloss;                  /* per-wave partial sums of the fused L2 loss */
   int64_t off_big, off_bign;          /* per-workgroup lists of large triangles, lengths + offsets */
-  int64_t big_tiles;                  /* see mer_tuning */
+  int64_t big_tiles;                  /* small_px <= 0: see mer_tuning; else the coarse tiles:
+                                         their number << 8 | log2 of their side */
   int64_t n_bingroups, off_bigflat;   /* workgroups of the binning passes; the packed list */
   int64_t off_bigpart;                /* scan partials of the list lengths */
-  int64_t ct_log2, total_ctiles;      /* coarse tiles: log2 of their side, their number */
-  int64_t off_ccount, off_ctile;      /* coarse tile counters; their lists and places */
-} mer_plan;
+} mer_plan;       /* 232 bytes in version 1: a plan lies in the caller's memory */
 
 /* One pinhole camera per view for the vertex transform: the rows of R are
  * the camera axes in world coordinates (x right, y down, z forward), C the

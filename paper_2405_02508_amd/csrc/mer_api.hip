@@ -11,7 +11,7 @@ namespace {
 
 constexpr int kVersion = 1;
 
-int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
+using mer::align256;
 
 // Log2 of the coarse tiles' side.  A workgroup takes one tile, so there have
 // to be enough of them for 256 compute units: 32 x 32 pixels from 2048 tiles
@@ -122,12 +122,11 @@ int mer_plan_init(const mer_view* views, int n_views, const mer_tuning* tun, mer
   off = align256(off + (bin_groups + 1023) / 1024 * 8);
   P->off_bigflat = off;
   off = align256(off + tris * 4);
-  P->ct_log2 = coarse_log2(tiles32, btiles, tris);
-  P->total_ctiles = P->ct_log2 == 5 ? tiles32 : P->ct_log2 == 4 ? btiles : tiles8;
-  P->off_ccount = off;
-  off = align256(off + P->total_ctiles * 8);
-  P->off_ctile = off;
-  off = align256(off + P->total_ctiles * 16);
+  if (P->small_px > 0) {
+    const int ctl = coarse_log2(tiles32, btiles, tris);
+    P->big_tiles = (ctl == 5 ? tiles32 : ctl == 4 ? btiles : tiles8) << 8 | ctl;
+    off = mer::coarse_plan(P).end;
+  }
   P->ws_bytes = off;
   return MER_OK;
 }

@@ -881,14 +881,15 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
   long long* tri_base = (long long*)(w + P->off_viewtab);
   long long* tile_base = tri_base + (P->n_views + 1);
   long long* status = (long long*)(w + P->off_status);
-  int2* count = (int2*)(w + P->off_ccount);
-  CTile* tiles = (CTile*)(w + P->off_ctile);
+  const CoarsePlan cp = coarse_plan(P);
+  int2* count = (int2*)(w + cp.off_count);
+  CTile* tiles = (CTile*)(w + cp.off_tile);
   uint2* seg = (uint2*)(w + P->off_rec);
   int* bins = (int*)(w + P->off_bins);
   int* seg_n = (int*)(w + P->off_bign);
   int* large = (int*)(w + P->off_bigflat);
-  const int ctl = (int)P->ct_log2;
-  const long long nt = P->total_ctiles;
+  const int ctl = cp.ctl;
+  const long long nt = cp.n;
   const int direct = P->n_views == 1 && nt * ((P->total_tris + 255) / 256) <= kDirectChunks;
   if (!direct) {
     hipLaunchKernelGGL(k_cinit, dim3((unsigned)min((nt + 1023) / 1024, 512ll)), dim3(1024), 0, st, views, P->n_views,

@@ -7,6 +7,27 @@
 namespace mer {
 constexpr int kBinBlock = 256;  // threads per workgroup of the binning passes (one triangle each)
 
+// The coarse tiles of a plan (small_px > 0) and their regions of the
+// workspace, after the last one mer_plan names: mer_plan lies in the caller's
+// memory, so its size belongs to the ABI and these are worked out where they
+// are used.
+struct CoarsePlan {
+  int ctl;                       // log2 of the tiles' side
+  int64_t n;                     // tiles
+  int64_t off_count, off_tile;   // int2 and CTile per tile
+  int64_t end;
+};
+inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
+inline CoarsePlan coarse_plan(const mer_plan* P) {
+  CoarsePlan c;
+  c.ctl = (int)(P->big_tiles & 255);
+  c.n = P->big_tiles >> 8;
+  c.off_count = align256(P->off_bigflat + P->total_tris * 4);
+  c.off_tile = align256(c.off_count + c.n * 8);
+  c.end = align256(c.off_tile + c.n * 16);
+  return c;
+}
+
 // attr/out (nullable): interpolate in the resolve, as launch_interpolate
 // would; tail as in ResolveOut
 int launch_rasterize(const mer_plan* P, const mer_view* views, const float* v, const int32_t* tri, int32_t* tri_id,

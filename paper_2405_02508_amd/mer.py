@@ -50,9 +50,12 @@ class Plan(ctypes.Structure):
                 ("total_v", ctypes.c_int64), ("off_vbase", ctypes.c_int64), ("off_bloss", ctypes.c_int64),
                 ("off_big", ctypes.c_int64), ("off_bign", ctypes.c_int64),
                 ("big_tiles", ctypes.c_int64), ("n_bingroups", ctypes.c_int64), ("off_bigflat", ctypes.c_int64),
-                ("off_bigpart", ctypes.c_int64),
-                ("ct_log2", ctypes.c_int64), ("total_ctiles", ctypes.c_int64),
-                ("off_ccount", ctypes.c_int64), ("off_ctile", ctypes.c_int64)]
+                ("off_bigpart", ctypes.c_int64)]
+
+    # coarse tiles of a plan that bins into them (small_px > 0): log2 of their
+    # side, and their number
+    ct_log2 = property(lambda self: self.big_tiles & 255 if self.small_px > 0 else 0)
+    total_ctiles = property(lambda self: self.big_tiles >> 8 if self.small_px > 0 else 0)
 
 
 class Camera(ctypes.Structure):
