@@ -10,7 +10,7 @@
 //   k_clarge   the same for triangles over many tiles, a workgroup each
 //   k_calloc   one thread per coarse tile: its range of the bin pool
 //   k_cfill    the ranked entries copied to their lists (no tests, no atomics)
-//   k_craster  one workgroup per coarse tile
+//   k_craster  one workgroup per coarse tile, or several where its list is long
 //
 // What this replaced listed every triangle in 8 x 8 tiles (count, scan, fill)
 // and rasterized triangles of at most 16 centres with global atomics: fifteen
@@ -39,8 +39,19 @@ constexpr unsigned kRankMax = (1u << kRankBits) - 1u;
 // fit (every triangle of the view is scanned instead); view and tile position.
 struct __align__(16) CTile {
   int base, n, view;
-  unsigned xy;  // column | row << 16
+  unsigned xy;  // column | row << 16 | kSplit
 };
+constexpr unsigned kSplit = 1u << 31;  // the list is split: items take its parts
+
+// One part of a long list, as a tile with that part of the entries (n < 0: no
+// part).  A tile's parts lie one after another, each a workgroup of its own;
+// they meet in the key image (64-bit maxima in memory), and the one that
+// finishes last writes the tile's pixels.  done counts them, in the first.
+struct CItem {
+  CTile t;
+  int part, parts, done, pad;
+};
+static_assert(sizeof(CItem) == kItemBytes, "the plan's region of them");
 
 __global__ void __launch_bounds__(1024) k_cinit(const mer_view* __restrict__ views, int n_views, int ctl,
                                                 long long* __restrict__ tri_base, long long* __restrict__ tile_base,
@@ -333,12 +344,18 @@ __global__ void __launch_bounds__(kBinBlock) k_clarge(const mer_view* __restrict
 // ---------------------------------------------------------- ranges and fill
 // Ranges need no order, so a workgroup of tiles takes its part of the pool
 // with one add.  Ranked entries come first in a tile's list, walked ones
-// after them.
+// after them.  A list longer than two parts is split while there is room for
+// its parts (their number in status[3]), and its tile's keys are cleared.
 __global__ void __launch_bounds__(256) k_calloc(const mer_view* __restrict__ views, int n_views, int ctl,
                                                 const long long* __restrict__ tile_base, long long n_tiles,
                                                 const int2* __restrict__ count, long long bin_cap,
-                                                CTile* __restrict__ tiles, long long* __restrict__ status) {
+                                                CTile* __restrict__ tiles, int item, int n_items,
+                                                CItem* __restrict__ items, unsigned long long* __restrict__ key,
+                                                long long* __restrict__ status) {
   __shared__ long long s_wave[4], s_base;
+  __shared__ CTile s_split[256];
+  __shared__ int s_nsplit;
+  if (threadIdx.x == 0) s_nsplit = 0;
   const long long g = (long long)blockIdx.x * 256 + threadIdx.x;
   const int2 c = g < n_tiles ? count[g] : make_int2(0, 0);
   const long long n = (long long)c.x + c.y;
@@ -356,16 +373,40 @@ __global__ void __launch_bounds__(256) k_calloc(const mer_view* __restrict__ vie
   const bool over = base + n > bin_cap || (unsigned)c.x >= kRankMax;
   const unsigned long long m = __ballot(over && g < n_tiles && n > 0);
   if (m && lane == 0) atomicAdd((unsigned long long*)status, (unsigned long long)__popcll(m));
-  if (g >= n_tiles) return;
-  const int vi = wave_bucket(tile_base, n_views, g);
-  int tx, ty;
-  grid_xy(g - tile_base[vi], (views[vi].W + (1 << ctl) - 1) >> ctl, tx, ty);
-  CTile t;
-  t.base = over ? 0 : (int)base;
-  t.n = n == 0 ? 0 : over ? -1 : (int)n;
-  t.view = vi;
-  t.xy = (unsigned)tx | (unsigned)ty << 16;
-  tiles[g] = t;
+  if (g < n_tiles) {
+    const int vi = wave_bucket(tile_base, n_views, g);
+    int tx, ty;
+    grid_xy(g - tile_base[vi], (views[vi].W + (1 << ctl) - 1) >> ctl, tx, ty);
+    CTile t;
+    t.base = over ? 0 : (int)base;
+    t.n = n == 0 ? 0 : over ? -1 : (int)n;
+    t.view = vi;
+    t.xy = (unsigned)tx | (unsigned)ty << 16;
+    if (n_items > 0 && t.n > max(kLongList, 2 * item)) {
+      const int want = (t.n + item - 1) / item;
+      const long long at = (long long)atomicAdd((unsigned long long*)status + 3, (unsigned long long)want);
+      const int got = (int)max(min((long long)want, n_items - at), 0ll);
+      if (got > 1) {
+        s_split[atomicAdd(&s_nsplit, 1)] = t;
+        t.xy |= kSplit;
+      }
+      const int size = ((t.n + max(got, 1) - 1) / max(got, 1) + 255) & ~255;
+      for (int i = 0; i < got; ++i) {
+        const int lo = (int)min((long long)i * size, (long long)t.n);
+        items[at + i] = {{t.base + lo, got > 1 ? min(size, t.n - lo) : -1, t.view, t.xy}, i, got, 0, 0};
+      }
+    }
+    tiles[g] = t;
+  }
+  __syncthreads();
+  for (int i = 0; i < s_nsplit; ++i) {
+    const mer_view vw = views[s_split[i].view];
+    const int x0 = (int)(s_split[i].xy & 0xffffu) << ctl, y0 = (int)(s_split[i].xy >> 16) << ctl;
+    for (int k = threadIdx.x; k < 1 << 2 * ctl; k += 256) {
+      const int x = x0 + (k & ((1 << ctl) - 1)), y = y0 + (k >> ctl);
+      if (x < vw.W && y < vw.H) key[vw.px_off + (long long)y * vw.W + x] = 0ull;
+    }
+  }
 }
 
 // The first n_groups workgroups copy the count pass's entries, the others
@@ -444,12 +485,17 @@ constexpr int kMaskGen = 16;  // bit of the candidate's tile mask: general recor
 // takes its 8 x 8 tiles, one lane per pixel, and walks the mask bits: a
 // candidate is skipped once no pixel's surface is as far as its bound.
 // direct: no lists; the plan's one view has few triangles and every tile
-// scans them all.
+// scans them all.  n_split workgroups of the grid, from split0 on, take the
+// parts of long lists, as many as there are, the others a tile each.  One workgroup for a
+// list whatever its length made 1.8 M triangles over 64 px of a 2048 x 2048
+// view take 483 us (104 in parts), and over 200 px 1088 (168).
 // STAGED: the resolve writes its image rows by way of LDS (below).
 template <int CTL, int NT, bool STAGED>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_craster(const mer_view* __restrict__ views, const CTile* __restrict__ tiles,
                                                  const int2* __restrict__ count, const int* __restrict__ bins,
                                                  const long long* __restrict__ tri_base, int direct, ResolveOut R,
+                                                 int split0, int n_split, CItem* __restrict__ items,
+                                                 unsigned long long* __restrict__ key,
                                                  long long* __restrict__ status) {
   constexpr int CT = 1 << CTL, NPX = CT * CT, NF = NPX / 64, FX = CT / 8, NW = NT / 64;
   constexpr int kChunk = NT;  // candidates taken at a time
@@ -462,24 +508,32 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
   __shared__ float s_mm[2 * NW];
   __shared__ int s_culled, s_next;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const long long g = xcd_tile(blockIdx.x, gridDim.x);
+  const int sb = (int)blockIdx.x - split0;
   CTile T;
-  if (direct) {
-    const int tiles_x = (views[0].W + CT - 1) >> CTL;
-    const unsigned q = (unsigned)g / (unsigned)tiles_x;
-    T.base = 0;
-    T.n = -1;
-    T.view = 0;
-    T.xy = ((unsigned)g - q * tiles_x) | q << 16;
+  if (__builtin_expect((unsigned)sb < (unsigned)n_split, 0)) {
+    if ((long long)sb >= status[3]) return;
+    T = items[sb].t;
+    if (T.n < 0) return;
   } else {
-    T = tiles[g];
-    // integrity: the fill pass takes every walked count back to 0
-    if (tid == 0 && count[g].y != 0) atomicAdd((unsigned long long*)status + 6, 1ull);
+    const long long g = xcd_tile((int)blockIdx.x - (sb < 0 ? 0 : n_split), (int)gridDim.x - n_split);
+    if (direct) {
+      const int tiles_x = (views[0].W + CT - 1) >> CTL;
+      const unsigned q = (unsigned)g / (unsigned)tiles_x;
+      T.base = 0;
+      T.n = -1;
+      T.view = 0;
+      T.xy = ((unsigned)g - q * tiles_x) | q << 16;
+    } else {
+      T = tiles[g];
+      // integrity: the fill pass takes every walked count back to 0
+      if (tid == 0 && count[g].y != 0) atomicAdd((unsigned long long*)status + 6, 1ull);
+      if (T.xy & kSplit) return;
+    }
   }
   const mer_view vw = views[T.view];
-  const int x0 = (int)(T.xy & 0xffffu) << CTL, y0 = (int)(T.xy >> 16) << CTL;
+  const int x0 = (int)(T.xy & 0xffffu) << CTL, y0 = (int)(T.xy >> 16 & 0x7fffu) << CTL;
   const int tb = direct ? 0 : (int)tri_base[T.view];
-  const int n_items = T.n < 0 ? vw.n_t : T.n;
+  int n_items = T.n < 0 ? vw.n_t : T.n;
   // keys are swizzled by row so that the rows of an 8 x 8 tile fall on
   // different banks
   auto key_at = [&](int x, int y) -> int { return (y << CTL) + (x ^ ((y & (CT / 8 - 1)) << 3)); };
@@ -516,7 +570,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
     s.ok = false;
     if (t >= 0) s = T.n >= 0 ? snap_visible(R.v, vw, row) : snap_triangle(R.v, vw, row);
     t_next = candidate(c0 + kChunk);
-    if (direct && t >= 0 && !s.ok && g == 0) atomicAdd(&s_culled, 1);
+    if (direct && t >= 0 && !s.ok && blockIdx.x == 0) atomicAdd(&s_culled, 1);
     PixBox b = {1, 1, 0, 0};
     if (s.ok) {
       b = pixel_box(s, vw);
@@ -799,7 +853,39 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
     }
   }
   __syncthreads();
-  if (direct && g == 0 && tid < 8) status[tid] = tid == 1 ? (long long)(n_items > 0 ? s_culled : 0) : 0;
+  if (__builtin_expect((T.xy & kSplit) != 0u, 0)) {
+    int b = (int)blockIdx.x - split0;
+    asm volatile("" : "+s"(b));  // read again: not kept through the loops
+    const int part = items[b].part, parts = items[b].parts;
+    // Every access here is an atomic that returns its old value, so it has
+    // taken place in memory, whichever L2 a workgroup sits behind, before the
+    // wave goes on.  Fences instead write the L2 back: 120 and 286 us for the
+    // two meshes above.
+    unsigned long long* kv = key + vw.px_off;
+    unsigned long long seen = 0;
+    if (n_items > 0) {
+#pragma unroll 1
+      for (int i = tid; i < NPX; i += NT) {
+        const int x = i & (CT - 1), y = i >> CTL;
+        const unsigned long long k = x0 + x < vw.W && y0 + y < vw.H ? s_key[key_at(x, y)] : 0ull;
+        if (k) seen |= atomicMax(kv + (long long)(y0 + y) * vw.W + x0 + x, k);
+      }
+    }
+    asm volatile("" ::"v"(seen));
+    __syncthreads();  // the part's maxima are in memory
+    if (tid == 0) s_next = atomicAdd(&items[b - part].done, 1);
+    __syncthreads();
+    if (s_next != parts - 1) return;
+#pragma unroll 1
+    for (int i = tid; i < NPX; i += NT) {
+      const int x = i & (CT - 1), y = i >> CTL;
+      if (x0 + x < vw.W && y0 + y < vw.H)
+        s_key[key_at(x, y)] = atomicMax(kv + (long long)(y0 + y) * vw.W + x0 + x, 0ull);
+    }
+    n_items = 1;  // the tile's keys are in LDS
+    __syncthreads();
+  }
+  if (direct && blockIdx.x == 0 && tid < 8) status[tid] = tid == 1 ? (long long)(n_items > 0 ? s_culled : 0) : 0;
   // ---- resolve, a row of the tile at a time.  STAGED: the image rows go
   // through the wave's part of the records' memory, and the wave writes them as
   // spans of consecutive floats.
@@ -888,6 +974,8 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
   int* bins = (int*)(w + P->off_bins);
   int* seg_n = (int*)(w + P->off_bign);
   int* large = (int*)(w + P->off_bigflat);
+  CItem* items = (CItem*)(w + cp.off_item);
+  unsigned long long* key = (unsigned long long*)(w + P->off_key) - P->px_begin;  // by pixel
   const int ctl = cp.ctl;
   const long long nt = cp.n;
   const int direct = P->n_views == 1 && nt * ((P->total_tris + 255) / 256) <= kDirectChunks;
@@ -901,15 +989,19 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
                          tile_base, ctl, large, status, count);
     }
     hipLaunchKernelGGL(k_calloc, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, views, P->n_views, ctl, tile_base,
-                       nt, count, P->bin_cap, tiles, status);
+                       nt, count, P->bin_cap, tiles, (int)cp.item, (int)cp.n_items, items, key, status);
     if (P->total_tris > 0)
       hipLaunchKernelGGL(k_cfill, dim3((unsigned)P->n_bingroups + kLargeGrid), dim3(kBinBlock), 0, st, views, P->n_views,
                          R.v, R.tri, tri_base, tile_base, ctl, (int)P->n_bingroups, count, seg, seg_n, large, status,
                          tiles, bins);
   }
+  // Parts go first in the grid, so as not to be its tail (1.8 M triangles over
+  // 64 px: 104 us, 109 when last), but last where there is room for few, since
+  // in front they delay the tiles when there are none: 1936 of them by 3 us.
+  const int n_split = direct ? 0 : (int)cp.n_items, split0 = n_split >= 2048 ? 0 : (int)nt;
 #define MER_CRASTER(CTL, ST)                                                                                          \
-  hipLaunchKernelGGL((k_craster<CTL, 256, ST>), dim3((unsigned)nt), dim3(256), 0, st, views, tiles, count, bins,      \
-                     tri_base, direct, R, status)
+  hipLaunchKernelGGL((k_craster<CTL, 256, ST>), dim3((unsigned)(nt + n_split)), dim3(256), 0, st, views, tiles,       \
+                     count, bins, tri_base, direct, R, split0, n_split, items, key, status)
   const bool staged = staged_rows(R, ctl);
   if (ctl == 5 && staged) MER_CRASTER(5, true);
   else if (ctl == 5) MER_CRASTER(5, false);

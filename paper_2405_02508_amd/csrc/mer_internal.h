@@ -7,6 +7,9 @@
 namespace mer {
 constexpr int kBinBlock = 256;  // threads per workgroup of the binning passes (one triangle each)
 
+constexpr int kLongList = 4096;  // entries of a coarse tile that one workgroup takes: sixteen rounds, about 40 us
+constexpr int kItemBytes = 32;
+
 // The coarse tiles of a plan (small_px > 0) and their regions of the
 // workspace, after the last one mer_plan names: mer_plan lies in the caller's
 // memory, so its size belongs to the ABI and these are worked out where they
@@ -15,6 +18,7 @@ struct CoarsePlan {
   int ctl;                       // log2 of the tiles' side
   int64_t n;                     // tiles
   int64_t off_count, off_tile;   // int2 and CTile per tile
+  int64_t item, n_items, off_item;  // long lists: entries per part, parts at most, CItem per part
   int64_t end;
 };
 inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
@@ -24,7 +28,15 @@ inline CoarsePlan coarse_plan(const mer_plan* P) {
   c.n = P->big_tiles >> 8;
   c.off_count = align256(P->off_bigflat + P->total_tris * 4);
   c.off_tile = align256(c.off_count + c.n * 8);
-  c.end = align256(c.off_tile + c.n * 16);
+  c.off_item = align256(c.off_tile + c.n * 16);
+  // Lists longer than kLongList and than two parts are split (mer_coarse.h).
+  // A part is 1024 entries, or as many as make 4096 parts of two entries a
+  // triangle; no list of a plan with fewer triangles is as long.  1.8 M
+  // triangles over 64 / 200 px of a 2048 x 2048 view, parts of 512, 1024 and
+  // 2048 entries: 102 / 167, 102 / 167 and 110 / 159 us.
+  c.item = P->total_tris > 2048 * 1024 ? (P->total_tris / 2048 + 255) & ~(int64_t)255 : 1024;
+  c.n_items = P->total_tris > kLongList ? (2 * P->total_tris / c.item + 7) & ~(int64_t)7 : 0;
+  c.end = align256(c.off_item + c.n_items * kItemBytes);
   return c;
 }
 
