@@ -944,10 +944,20 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
 }
 
 // ------------------------------------------------------------------ launch
-// A small view of few triangles needs no lists: where all tiles together
-// have at most this many chunks of candidates to look at, every tile scans
-// every triangle, in one launch instead of five.
-constexpr int kDirectChunks = 512;
+// A small view of few triangles needs no lists: where each tile has at most
+// kDirectPerTile chunks of candidates to look at, and all together at most
+// kDirectChunks, every tile scans every triangle, in one launch instead of
+// six.  A chunk takes a tile's workgroup 2 to 3 us, the lists 15 to 20: without
+// / with lists, us, 16 tiles of 4 chunks 21 / 27, 7 27 / 26, 10 33 / 25, 16
+// 45 / 26; 64 tiles of 8 chunks 26 / 29; 4 tiles of 125 240 / 25.  The total's
+// line is not where the two meet: 242 tiles of 2 chunks 11 / 38 on this side of
+// it, 484 12 / 37 and 3249 32 / 45 on the other.
+constexpr int kDirectChunks = 512, kDirectPerTile = 8;
+
+static bool direct_tiles(const mer_plan* P, long long n_tiles) {
+  const long long chunks = (P->total_tris + 255) / 256;
+  return P->n_views == 1 && chunks <= kDirectPerTile && n_tiles * chunks <= kDirectChunks;
+}
 
 // Image rows that no vector store takes whole (other than 3, 4, 8, ... floats)
 // are written a float a lane, C lines a store; from some width on it is faster
@@ -978,7 +988,7 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
   unsigned long long* key = (unsigned long long*)(w + P->off_key) - P->px_begin;  // by pixel
   const int ctl = cp.ctl;
   const long long nt = cp.n;
-  const int direct = P->n_views == 1 && nt * ((P->total_tris + 255) / 256) <= kDirectChunks;
+  const int direct = direct_tiles(P, nt);
   if (!direct) {
     hipLaunchKernelGGL(k_cinit, dim3((unsigned)min((nt + 1023) / 1024, 512ll)), dim3(1024), 0, st, views, P->n_views,
                        ctl, tri_base, tile_base, status, count, nt);
