@@ -82,16 +82,22 @@ __device__ __forceinline__ PixBox pixel_box(const Snap& s, const mer_view& vw) {
   return b;
 }
 
-// A workgroup over one large triangle's coarse tiles; f(tile) for the tiles it
-// may cover.  The listed triangles go to the grid's workgroups `first`,
-// first + 1, ... in turn.
+// One large triangle's coarse tiles over a workgroup's lanes, or over a wave's
+// where there are more triangles than workgroups; f(triangle, tile) for the
+// tiles it may cover.  The listed triangles go to the grid's workgroups
+// `first`, first + 1, ..., or to their waves, in turn (200,000 triangles over
+// about 20 tiles each: k_clarge 86 us by workgroups, 37 by waves).
 template <typename F>
 __device__ __forceinline__ void walk_large(const mer_view* __restrict__ views, int n_views,
                                            const long long* __restrict__ tri_base,
                                            const long long* __restrict__ tile_base, const float* __restrict__ v,
                                            const int32_t* __restrict__ tri, int ctl, const int* __restrict__ large,
                                            int n_large, int first, F f) {
-  for (int i = (int)blockIdx.x - first; i < n_large; i += (int)gridDim.x - first) {
+  const int b0 = (int)blockIdx.x - first, nb = (int)gridDim.x - first;
+  const bool waves = n_large > nb;
+  const int lanes = waves ? 64 : kBinBlock, lane = threadIdx.x & (lanes - 1);
+  const int step = waves ? nb * (kBinBlock / 64) : nb;
+  for (int i = waves ? b0 * (kBinBlock / 64) + (threadIdx.x >> 6) : b0; i < n_large; i += step) {
     const int g = __builtin_amdgcn_readfirstlane(large[i]);
     const int vi = __builtin_amdgcn_readfirstlane(find_bucket(tri_base, n_views, g));
     const mer_view vw = views[vi];
@@ -100,7 +106,7 @@ __device__ __forceinline__ void walk_large(const mer_view* __restrict__ views, i
     const Rec R = make_rec(s);
     const int tx0 = b.x0 >> ctl, ty0 = b.y0 >> ctl, ntx = (b.x1 >> ctl) - tx0 + 1, nty = (b.y1 >> ctl) - ty0 + 1;
     const int tiles_x = (vw.W + (1 << ctl) - 1) >> ctl;
-    for (int k = threadIdx.x; k < ntx * nty; k += kBinBlock) {
+    for (int k = lane; k < ntx * nty; k += lanes) {
       const int dy = (int)((unsigned)k / (unsigned)ntx), tx = tx0 + k - dy * ntx, ty = ty0 + dy;
       if (box_may_cover(R, max(tx << ctl, b.x0), max(ty << ctl, b.y0), min(((tx + 1) << ctl) - 1, b.x1),
                         min(((ty + 1) << ctl) - 1, b.y1)))
@@ -326,9 +332,10 @@ __global__ void __launch_bounds__(kBinBlock) k_ccount(const mer_view* __restrict
   if (m && lane == 0) atomicAdd((unsigned long long*)status + 1, (unsigned long long)__popcll(m));
 }
 
-// Workgroups for the large triangles, whether there are any or not: 16 views of
-// few large triangles take 9 us in k_clarge and 13 in the fill (256 workgroups
-// 19 and 30), and an empty list costs the same 4 to 5 us with either.
+// Workgroups for the large triangles, whether there are any or not.  us in
+// k_clarge and in the fill with 256, 1024 and 2048: 16 views of few large
+// triangles 8.7 + 9.4, 4.9 + 5.4, 4.9 + 5.5; 200,000 of up to 60 px in one of
+// 1024 x 1024 89 + 111, 37 + 56, 32 + 41; none 1.6 + 2.6, 1.8 + 2.7, 1.9 + 2.7.
 constexpr int kLargeGrid = 1024;
 
 __global__ void __launch_bounds__(kBinBlock) k_clarge(const mer_view* __restrict__ views, int n_views,
@@ -348,7 +355,7 @@ __global__ void __launch_bounds__(kBinBlock) k_clarge(const mer_view* __restrict
 // its parts (their number in status[3]), and its tile's keys are cleared.
 __global__ void __launch_bounds__(256) k_calloc(const mer_view* __restrict__ views, int n_views, int ctl,
                                                 const long long* __restrict__ tile_base, long long n_tiles,
-                                                const int2* __restrict__ count, long long bin_cap,
+                                                int2* __restrict__ count, long long bin_cap,
                                                 CTile* __restrict__ tiles, int item, int n_items,
                                                 CItem* __restrict__ items, unsigned long long* __restrict__ key,
                                                 long long* __restrict__ status) {
@@ -397,6 +404,7 @@ __global__ void __launch_bounds__(256) k_calloc(const mer_view* __restrict__ vie
       }
     }
     tiles[g] = t;
+    if (c.y > 0) count[g].x = over ? -1 : t.base + c.x;  // where the walked ones go
   }
   __syncthreads();
   for (int i = 0; i < s_nsplit; ++i) {
@@ -421,9 +429,13 @@ __global__ void __launch_bounds__(kBinBlock) k_cfill(const mer_view* __restrict_
                                                      const CTile* __restrict__ tiles, int* __restrict__ bins) {
   if ((int)blockIdx.x >= n_groups) {
     walk_large(views, n_views, tri_base, tile_base, v, tri, ctl, large, (int)status[4], n_groups, [&](int g, int ct) {
-      const int2 t = *reinterpret_cast<const int2*>(&tiles[ct]);
-      const int k = atomicSub(&count[ct].y, 1) - 1;
-      if (t.y >= 0) bins[t.x + count[ct].x + k] = g;
+      // both counters in one access: the place is the first one's value (-1:
+      // no room) plus the second's, which goes down.  Read by loads of their
+      // own beside the atomics, 100,000 triangles' 650,000 entries in 1024
+      // tiles took 199 us, and take 40.
+      const unsigned long long c = atomicAdd(reinterpret_cast<unsigned long long*>(&count[ct]), ~0ull << 32);
+      const int at = (int)(unsigned)c;
+      if (at >= 0) bins[at + (int)(c >> 32) - 1] = g;
     });
     return;
   }
