@@ -39,14 +39,15 @@ constexpr unsigned kRankMax = (1u << kRankBits) - 1u;
 // fit (every triangle of the view is scanned instead); view and tile position.
 struct __align__(16) CTile {
   int base, n, view;
-  unsigned xy;  // column | row << 16 | kSplit
+  unsigned xy;  // column | row << 16, and the bits below
 };
-constexpr unsigned kSplit = 1u << 31;  // the list is split: items take its parts
+constexpr unsigned kPart = 1u << 31;   // a part of a long list (CItem)
+constexpr unsigned kGone = 1u << 15;   // nothing to do: the list is split, or no part
 
-// One part of a long list, as a tile with that part of the entries (n < 0: no
-// part).  A tile's parts lie one after another, each a workgroup of its own;
-// they meet in the key image (64-bit maxima in memory), and the one that
-// finishes last writes the tile's pixels.  done counts them, in the first.
+// One part of a long list, as a tile with that part of the entries.  A tile's
+// parts lie one after another, each a workgroup of its own; they meet in the
+// key image (64-bit maxima in memory), and the one that finishes last writes
+// the tile's pixels.  done counts them, in the first.
 struct CItem {
   CTile t;
   int part, parts, done, pad;
@@ -56,7 +57,8 @@ static_assert(sizeof(CItem) == kItemBytes, "the plan's region of them");
 __global__ void __launch_bounds__(1024) k_cinit(const mer_view* __restrict__ views, int n_views, int ctl,
                                                 long long* __restrict__ tri_base, long long* __restrict__ tile_base,
                                                 long long* __restrict__ status, int2* __restrict__ count,
-                                                long long n_tiles) {
+                                                long long n_tiles, CItem* __restrict__ items, int n_items) {
+  for (int i = (int)(blockIdx.x * 1024 + threadIdx.x); i < n_items; i += (int)gridDim.x * 1024) items[i].t.xy = kGone;
   for (long long i = (long long)blockIdx.x * 1024 + threadIdx.x; i < n_tiles; i += (long long)gridDim.x * 1024)
     count[i] = make_int2(0, 0);
   if (blockIdx.x == 0) view_prefix(views, n_views, ctl, ctl, tri_base, tile_base, status);
@@ -395,12 +397,12 @@ __global__ void __launch_bounds__(256) k_calloc(const mer_view* __restrict__ vie
       const int got = (int)max(min((long long)want, n_items - at), 0ll);
       if (got > 1) {
         s_split[atomicAdd(&s_nsplit, 1)] = t;
-        t.xy |= kSplit;
-      }
-      const int size = ((t.n + max(got, 1) - 1) / max(got, 1) + 255) & ~255;
-      for (int i = 0; i < got; ++i) {
-        const int lo = (int)min((long long)i * size, (long long)t.n);
-        items[at + i] = {{t.base + lo, got > 1 ? min(size, t.n - lo) : -1, t.view, t.xy}, i, got, 0, 0};
+        const int size = ((t.n + got - 1) / got + 255) & ~255;
+        for (int i = 0; i < got; ++i) {
+          const int lo = (int)min((long long)i * size, (long long)t.n);
+          items[at + i] = {{t.base + lo, min(size, t.n - lo), vi, t.xy | kPart}, i, got, 0, 0};
+        }
+        t.xy |= kGone;
       }
     }
     tiles[g] = t;
@@ -506,7 +508,7 @@ template <int CTL, int NT, bool STAGED>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_craster(const mer_view* __restrict__ views, const CTile* __restrict__ tiles,
                                                  const int2* __restrict__ count, const int* __restrict__ bins,
                                                  const long long* __restrict__ tri_base, int direct, ResolveOut R,
-                                                 int split0, int n_split, CItem* __restrict__ items,
+                                                 int split0, int n_split, int n_tiles, CItem* __restrict__ items,
                                                  unsigned long long* __restrict__ key,
                                                  long long* __restrict__ status) {
   constexpr int CT = 1 << CTL, NPX = CT * CT, NF = NPX / 64, FX = CT / 8, NW = NT / 64;
@@ -521,29 +523,24 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
   __shared__ int s_culled, s_next;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int sb = (int)blockIdx.x - split0;
+  const bool split = (unsigned)sb < (unsigned)n_split;
+  const long long g = xcd_tile((int)blockIdx.x - (sb < 0 ? 0 : n_split), n_tiles);
   CTile T;
-  if (__builtin_expect((unsigned)sb < (unsigned)n_split, 0)) {
-    if ((long long)sb >= status[3]) return;
-    T = items[sb].t;
-    if (T.n < 0) return;
+  if (direct) {
+    const int tiles_x = (views[0].W + CT - 1) >> CTL;
+    const unsigned q = (unsigned)g / (unsigned)tiles_x;
+    T.base = 0;
+    T.n = -1;
+    T.view = 0;
+    T.xy = ((unsigned)g - q * tiles_x) | q << 16;
   } else {
-    const long long g = xcd_tile((int)blockIdx.x - (sb < 0 ? 0 : n_split), (int)gridDim.x - n_split);
-    if (direct) {
-      const int tiles_x = (views[0].W + CT - 1) >> CTL;
-      const unsigned q = (unsigned)g / (unsigned)tiles_x;
-      T.base = 0;
-      T.n = -1;
-      T.view = 0;
-      T.xy = ((unsigned)g - q * tiles_x) | q << 16;
-    } else {
-      T = tiles[g];
-      // integrity: the fill pass takes every walked count back to 0
-      if (tid == 0 && count[g].y != 0) atomicAdd((unsigned long long*)status + 6, 1ull);
-      if (T.xy & kSplit) return;
-    }
+    T = *(split ? &items[sb].t : tiles + g);
+    // integrity: the fill pass takes every walked count back to 0
+    if (!split && tid == 0 && count[g].y != 0) atomicAdd((unsigned long long*)status + 6, 1ull);
+    if (T.xy & kGone) return;
   }
   const mer_view vw = views[T.view];
-  const int x0 = (int)(T.xy & 0xffffu) << CTL, y0 = (int)(T.xy >> 16 & 0x7fffu) << CTL;
+  const int x0 = (int)(T.xy & 0x7fffu) << CTL, y0 = (int)(T.xy >> 16 & 0x7fffu) << CTL;
   const int tb = direct ? 0 : (int)tri_base[T.view];
   int n_items = T.n < 0 ? vw.n_t : T.n;
   // keys are swizzled by row so that the rows of an 8 x 8 tile fall on
@@ -865,7 +862,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
     }
   }
   __syncthreads();
-  if (__builtin_expect((T.xy & kSplit) != 0u, 0)) {
+  if (__builtin_expect((T.xy & kPart) != 0u, 0)) {
     int b = (int)blockIdx.x - split0;
     asm volatile("" : "+s"(b));  // read again: not kept through the loops
     const int part = items[b].part, parts = items[b].parts;
@@ -1003,7 +1000,7 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
   const int direct = direct_tiles(P, nt);
   if (!direct) {
     hipLaunchKernelGGL(k_cinit, dim3((unsigned)min((nt + 1023) / 1024, 512ll)), dim3(1024), 0, st, views, P->n_views,
-                       ctl, tri_base, tile_base, status, count, nt);
+                       ctl, tri_base, tile_base, status, count, nt, items, (int)cp.n_items);
     if (P->total_tris > 0) {
       hipLaunchKernelGGL(k_ccount, dim3((unsigned)P->n_bingroups), dim3(kBinBlock), 0, st, views, P->n_views, R.v, R.tri,
                          tri_base, tile_base, (int)P->total_tris, ctl, count, seg, seg_n, large, status);
@@ -1023,7 +1020,7 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
   const int n_split = direct ? 0 : (int)cp.n_items, split0 = n_split >= 2048 ? 0 : (int)nt;
 #define MER_CRASTER(CTL, ST)                                                                                          \
   hipLaunchKernelGGL((k_craster<CTL, 256, ST>), dim3((unsigned)(nt + n_split)), dim3(256), 0, st, views, tiles,       \
-                     count, bins, tri_base, direct, R, split0, n_split, items, key, status)
+                     count, bins, tri_base, direct, R, split0, n_split, (int)nt, items, key, status)
   const bool staged = staged_rows(R, ctl);
   if (ctl == 5 && staged) MER_CRASTER(5, true);
   else if (ctl == 5) MER_CRASTER(5, false);
