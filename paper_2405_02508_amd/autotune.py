@@ -10,10 +10,14 @@ For a view table and its geometry the tuner:
   2. times mer_rasterize for each candidate with HIP events on the current
      stream and keeps the fastest.
 Choices are cached in a JSON file keyed by a shape class (view count,
-pixel and triangle counts rounded to powers of two).  An entry names the lists
-its pool was measured for: one with small_px >= 0 that does not say "coarse" is
-from before they existed, when triangles of few pixels took no entries, and is
-measured anew (a pool too small for its lists is exact but slow).
+pixel and triangle counts rounded to powers of two) and the side of the coarse
+tiles, since a pool belongs to its lists (one too small for them is exact but
+slow): within a class it grows with the pixels and triangles it is used for.  A
+plan that needs no lists (a small view of few triangles) measures no entries:
+it keeps the default pool, bin_cap 0.  Entries of a class alone are from before
+the side was part of the key: those of per-tile lists hold, those of coarse
+tiles get the default pool, and those from before there were coarse tiles, when
+triangles of few pixels took no entries, are measured anew.
 """
 from __future__ import annotations
 
@@ -51,17 +55,40 @@ def _load(path):
         return {}
 
 
+def _totals(views_i64):
+    V = np.asarray(views_i64, np.int64)
+    return int((V[:, 6] * V[:, 7]).sum()), int(V[:, 5].sum())
+
+
+def _reuse(data, views_i64):
+    """The cached choice for these views (without its measurements), or None."""
+    key = shape_class(views_i64)
+    hit = data.get(key)  # of a class alone
+    if hit and hit.get("small_px", 0) < 0:
+        return dict(hit)
+    if hit and hit.get("lists") == "coarse":
+        return dict(hit, bin_cap=0)
+    hit = data.get(_side_key(views_i64))
+    if not hit:
+        return None
+    px, tris = _totals(views_i64)
+    grow = max(1.0, px / hit["px"]) * max(1.0, tris / hit["tris"])
+    return dict(hit, bin_cap=min(int(hit["bin_cap"] * grow), 2**31 - 2))
+
+
+def _side_key(views_i64):
+    return f"{shape_class(views_i64)}-c{1 << mer.plan_init(views_i64).ct_log2}"
+
+
 def tune(views_i64, v, tri, device="cuda", candidates=CANDIDATES, reps=3, cache_path=DEFAULT_CACHE,
          use_cache=True, log=None):
     """Return dict(tile=(w, h), small_px=int, big_tiles=int, bin_cap=int, ms=float, table=[...])."""
     import torch
     key = shape_class(views_i64)
     if use_cache and cache_path:
-        hit = _load(cache_path).get(key)
-        if hit and (hit.get("small_px", 0) < 0 or hit.get("lists") == "coarse"):
-            hit["tile"] = tuple(hit["tile"])
-            hit["cached"] = True
-            return hit
+        hit = _reuse(_load(cache_path), views_i64)
+        if hit:
+            return dict(hit, tile=tuple(hit["tile"]), cached=True)
     n_px = int(mer.plan_init(views_i64).total_px)
     tid = torch.empty(n_px, dtype=torch.int32, device=device)
     depth = torch.empty(n_px, dtype=torch.float32, device=device)
@@ -73,7 +100,7 @@ def tune(views_i64, v, tri, device="cuda", candidates=CANDIDATES, reps=3, cache_
         ctx = mer.Context(views_i64, device=device, tile=(tw, th), small_px=sp, big_tiles=bt)
         ctx.rasterize(v, tri, tid, depth, bary)
         st = ctx.status()
-        cap = int(st["entries"] * 1.25) + 4096
+        cap = int(st["entries"] * 1.25) + 4096 if st["entries"] else 0
         del ctx
         ctx = mer.Context(views_i64, device=device, tile=(tw, th), small_px=sp, big_tiles=bt, bin_cap=cap)
         ctx.rasterize(v, tri, tid, depth, bary)
@@ -96,8 +123,9 @@ def tune(views_i64, v, tri, device="cuda", candidates=CANDIDATES, reps=3, cache_
     out = dict(best, table=table, key=key, cached=False)
     if cache_path:
         data = _load(cache_path)
-        data[key] = {k: out[k] for k in ("tile", "small_px", "big_tiles", "bin_cap", "entries", "ms")}
-        data[key]["lists"] = "tile" if out["small_px"] < 0 else "coarse"
+        px, tris = _totals(views_i64)
+        data[_side_key(views_i64)] = dict({k: out[k] for k in ("tile", "small_px", "big_tiles", "bin_cap", "entries", "ms")},
+                                          px=px, tris=max(tris, 1))
         os.makedirs(os.path.dirname(cache_path), exist_ok=True)
         tmp = cache_path + ".tmp"
         with open(tmp, "w") as f:
