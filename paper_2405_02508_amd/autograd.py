@@ -21,7 +21,8 @@ from . import mer
 
 
 class Renderer:
-    """Plan, workspace and topology for a fixed view table."""
+    """Plan, workspace and topology for a fixed view table (``tile``,
+    ``small_px``, ``bin_cap`` and ``big_tiles`` as ``mer.Context`` takes them)."""
 
     def __init__(self, views_i64, tri, device="cuda", tile=(8, 8), small_px=0, bin_cap=0,
                  append_z=False, mask_channel=False, store_bary=True, big_tiles=0):

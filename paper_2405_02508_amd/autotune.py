@@ -30,10 +30,9 @@ import numpy as np
 from . import mer
 
 CANDIDATES = (
-    # (tile_w, tile_h, small_px, big_tiles)
-    (8, 8, 16, 16), (8, 8, 16, -1), (8, 8, 64, 16), (8, 8, 256, 16),
-    (16, 16, 16, 16), (16, 16, 64, 16), (16, 16, 256, 16),
-    (32, 8, 64, 16), (16, 8, 64, 16),
+    # (tile_w, tile_h, small_px, big_tiles): the coarse tiles, whatever the
+    # other three are, and the per-tile lists (small_px < 0)
+    (8, 8, 16, 16),
     (8, 8, -1, 16), (8, 8, -1, -1), (16, 16, -1, 16),
 )
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "mer_autotune.json")
@@ -96,7 +95,12 @@ def tune(views_i64, v, tri, device="cuda", candidates=CANDIDATES, reps=3, cache_
     stream = torch.cuda.current_stream()
     table = []
     best = None
+    seen = set()
     for (tw, th, sp, bt) in candidates:
+        runs = (tw, th, bt) if sp < 0 else "coarse"  # what the candidate makes a plan of
+        if runs in seen:
+            continue
+        seen.add(runs)
         ctx = mer.Context(views_i64, device=device, tile=(tw, th), small_px=sp, big_tiles=bt)
         ctx.rasterize(v, tri, tid, depth, bary)
         st = ctx.status()

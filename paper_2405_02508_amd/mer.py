@@ -159,6 +159,11 @@ class Context:
 
     Owns nothing but torch tensors; every method is one C-ABI call on the
     current torch stream.
+
+    By default triangles are listed in coarse tiles, whose side the plan picks;
+    ``tile`` and ``big_tiles`` have an effect only with ``small_px`` < 0, which
+    lists them in tiles of that shape.  The results do not depend on any of
+    them, nor on ``bin_cap``.
     """
 
     def __init__(self, views_i64, device="cuda", tile=(8, 8), bin_cap=0, small_px=0, big_tiles=0):

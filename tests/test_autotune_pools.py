@@ -103,3 +103,14 @@ def test_an_entry_of_a_class_alone_keeps_the_default_pool(tmp_path):
     path.write_text(json.dumps({autotune.shape_class(V): entry}))
     got = autotune.tune(V, None, None, cache_path=str(path))
     assert got["cached"] and got["bin_cap"] == 0 and got["tile"] == (8, 8)
+
+
+def test_no_rasterizer_is_measured_twice(tmp_path, measured):
+    made, report = measured
+    V = _view(300, 300, 5000)
+    out = autotune.tune(V, None, None, device="cpu", cache_path=str(tmp_path / "t.json"))
+    coarse = [r for r in out["table"] if r["small_px"] >= 0]
+    assert len(coarse) == 1 and len(out["table"]) == len(autotune.CANDIDATES) == 4
+    same = ((8, 8, 16, 16), (16, 16, 256, -1), (32, 8, 64, 4), (8, 8, -1, 16), (8, 8, -3, 16))
+    out = autotune.tune(V, None, None, device="cpu", candidates=same, cache_path=None)
+    assert [(tuple(r["tile"]), r["small_px"]) for r in out["table"]] == [((8, 8), 16), ((8, 8), -1)]
