@@ -11,7 +11,11 @@ import ctypes
 import os
 
 import numpy as np
-import torch
+
+try:
+    import torch
+except ImportError:  # plans and the library's symbols need none of it
+    torch = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmer.so")
@@ -135,7 +139,7 @@ def plan_init(views_i64, tile=(8, 8), bin_cap=0, small_px=0, big_tiles=0) -> Pla
 # pointers go to ctypes as plain integers and the plan by itself, the stream
 # is asked for as its raw handle, and no argument is checked twice (a step on a
 # 64 x 64 view, two calls and three fills: 42 us to enqueue before, 35 now).
-_f32, _i32 = torch.float32, torch.int32
+_f32, _i32 = (torch.float32, torch.int32) if torch else (None, None)
 
 
 def _ptr(t):
