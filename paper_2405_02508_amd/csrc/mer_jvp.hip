@@ -61,10 +61,10 @@ __device__ __forceinline__ void frag_tangent(const TriTangent& g, const Snap& s,
   }
 }
 
-// One workgroup per 16 x 16 tile of one view, one thread per pixel, as in the
+// One workgroup per TS x TS tile of one view, one thread per pixel, as in the
 // backward sweep: each lane snaps its pixel's triangle once and publishes its
-// id and which neighbours' centres it holds; the first wave does so for the
-// 64 pixels around the tile.  A pair is classified from one bit of each side,
+// id and which neighbours' centres it holds; the first 4 TS lanes do so for
+// the pixels around the tile.  A pair is classified from one bit of each side,
 // and the side that is on top (both at an intersection) publishes its
 // fragment's tangent, once for all its pairs; then every pixel takes the edge
 // tangents dp of its four pairs (d4) from there, and per channel
@@ -75,27 +75,30 @@ __device__ __forceinline__ void frag_tangent(const TriTangent& g, const Snap& s,
 // Bound by vector issue: building a table of the tile's distinct triangles in
 // LDS first (a hash, then one snap each) and evaluating a pair's tangent on
 // both its sides took 795 instructions per wave and 1.28 ms on 128 scenes (54
-// M px, 3 channels); this takes JVP_NOW.
-constexpr int kJq = 256 + 64;  // tile pixels, then 16 around it per side: left, right, up, down
-
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_jvp(
+// M px, 3 channels); this takes 546 and 1.02.
+template <int TS>  // side of the tile: 8 or 16
+__global__ void __launch_bounds__(TS * TS) __attribute__((amdgpu_waves_per_eu(6))) k_jvp(
     const mer_view* __restrict__ views, int n_views, const long long* __restrict__ btile_base,
     const float* __restrict__ v, const int32_t* __restrict__ tri, const int32_t* __restrict__ tri_id,
     const float* __restrict__ attr, const float* __restrict__ dattr, int C_a, int append_z,
     const float* __restrict__ img, int C_e, const float* __restrict__ dv, int flags, float* __restrict__ dimg) {
+  constexpr int NP = TS * TS, kJq = NP + 4 * TS;  // tile pixels, then TS around it per side: left, right, up, down
   __shared__ int s_t[kJq];             // triangle, -1 background, outside the view or one that does not snap
   __shared__ unsigned char s_cm[kJq];  // bit d: that triangle holds the centre of neighbour d (0 left, 1 right, 2 up, 3 down)
   __shared__ float s_dr[3][kJq];       // fragment tangents (x, y, 1/z) of the pixels that are on top of some pair
-  const long long tile = xcd_tile(blockIdx.x, gridDim.x);
+  // 16 x 16 tiles; of 8 x 8 ones, four workgroups share one
+  constexpr int SUB = TS == 8 ? 2 : 0;
+  const long long part = xcd_tile(blockIdx.x, gridDim.x);
   long long local_tile;
-  const int vi = tile_view(btile_base, n_views, tile, local_tile);
+  const int vi = tile_view(btile_base, n_views, part >> SUB, local_tile);
   const mer_view vw = views[vi];
   int x0, y0;
   grid_xy(local_tile, (vw.W + 15) >> 4, x0, y0);
-  x0 *= 16;
-  y0 *= 16;
+  x0 = x0 * 16 + (SUB ? ((int)part & 1) * 8 : 0);
+  y0 = y0 * 16 + (SUB ? ((int)part >> 1 & 1) * 8 : 0);
+  if (SUB && (x0 >= vw.W || y0 >= vw.H)) return;
   const float* dvb = dv ? dv + vw.v_off * 3 : nullptr;
-  const int lt = threadIdx.x, lx = lt & 15, ly = lt >> 4;
+  const int lt = threadIdx.x, lx = lt % TS, ly = lt / TS;
   const int px = x0 + lx, py = y0 + ly;
   const bool inside = px < vw.W && py < vw.H;
   const long long p = vw.px_off + (long long)py * vw.W + px;
@@ -104,10 +107,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
 
   // a pixel around the tile (lanes of the first wave): its place, and the
   // tile pixel next to it
-  const int side = (lt & 63) >> 4, ri = lt & 15;
-  const int ix = side == 0 ? 0 : side == 1 ? 15 : ri, iy = side == 2 ? 0 : side == 3 ? 15 : ri;
-  const int qx = x0 + (side == 0 ? -1 : side == 1 ? 16 : ri), qy = y0 + (side == 2 ? -1 : side == 3 ? 16 : ri);
-  if (want_edge && lt < 64) {
+  const int side = lt / TS & 3, ri = lt % TS;
+  const int ix = side == 0 ? 0 : side == 1 ? TS - 1 : ri, iy = side == 2 ? 0 : side == 3 ? TS - 1 : ri;
+  const int qx = x0 + (side == 0 ? -1 : side == 1 ? TS : ri), qy = y0 + (side == 2 ? -1 : side == 3 ? TS : ri);
+  if (want_edge && lt < 4 * TS) {
     int rt = -1;
     if (qx >= 0 && qy >= 0 && qx < vw.W && qy < vw.H) rt = tri_id[vw.px_off + (long long)qy * vw.W + qx];
     if (rt >= vw.n_t) rt = -1;
@@ -117,8 +120,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
       if (!R.ok) rt = -1;
       else if (contains(R, x0 + ix, y0 + iy)) rc = 1u << (side ^ 1);
     }
-    s_t[256 + lt] = rt;
-    s_cm[256 + lt] = (unsigned char)rc;
+    s_t[NP + lt] = rt;
+    s_cm[NP + lt] = (unsigned char)rc;
   }
   int t = inside ? tri_id[p] : -1;
   if (t >= vw.n_t || t < 0) t = -1;
@@ -140,10 +143,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
     __syncthreads();
     // the place of neighbour d
     auto nq = [&](int d) -> int {
-      if (d == 0) return lx > 0 ? lt - 1 : 256 + ly;
-      if (d == 1) return lx < 15 ? lt + 1 : 256 + 16 + ly;
-      if (d == 2) return ly > 0 ? lt - 16 : 256 + 32 + lx;
-      return ly < 15 ? lt + 16 : 256 + 48 + lx;
+      if (d == 0) return lx > 0 ? lt - 1 : NP + ly;
+      if (d == 1) return lx < TS - 1 ? lt + 1 : NP + TS + ly;
+      if (d == 2) return ly > 0 ? lt - TS : NP + 2 * TS + lx;
+      return ly < TS - 1 ? lt + TS : NP + 3 * TS + lx;
     };
     // One side background: the other is on top.  Both covered: the side whose
     // centre the other triangle holds too, both sides at an intersection;
@@ -166,15 +169,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
 #pragma unroll
       for (int k = 0; k < 3; ++k) s_dr[k][lt] = dr[k];
     }
-    if (lt < 64) {
-      const int rt = s_t[256 + lt], it = iy * 16 + ix, ti = s_t[it];
-      const bool r_holds = (s_cm[256 + lt] >> (side ^ 1)) & 1u, i_holds = (s_cm[it] >> side) & 1u;
+    if (lt < 4 * TS) {
+      const int rt = s_t[NP + lt], it = iy * TS + ix, ti = s_t[it];
+      const bool r_holds = (s_cm[NP + lt] >> (side ^ 1)) & 1u, i_holds = (s_cm[it] >> side) & 1u;
       if (x0 + ix < vw.W && y0 + iy < vw.H && on_top(rt, ti, r_holds, i_holds)) {
         const Snap R = snap_triangle<false>(v, vw, tri_row(tri, vw, rt));
         float dr[3];
         frag_tangent(tri_tangent(dvb, R), R, qx, qy, dr);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) s_dr[k][256 + lt] = dr[k];
+        for (int k = 0; k < 3; ++k) s_dr[k][NP + lt] = dr[k];
       }
     }
     __syncthreads();  // the tangents are published
@@ -331,6 +334,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
   }
 }
 
+// Rows that no vector store takes are read and written a float at a time, and
+// the wave of a tile that has most of that to do holds its three neighbours'
+// place: 8 x 8 tiles, one wave each, finish on their own, though their border
+// is half their pixels.  us, 16 x 16 / 8 x 8 tiles (and before either), views of
+// 600 x 600 and 1000 x 1000: rows of 2 floats 28 / 28 (2 small views); of 7 52
+// / 44 (51), 16 large views 644 / 621 (720); of 11 75 / 60 (65), 8 large 498 /
+// 489, 16 978 / 960; of 17 117 / 94 (98), 2 large 222 / 198 (203), 4 483 / 500,
+// 16 1823 / 1912 (2004).
+static bool small_jvp_tiles(long long tiles16, int C_e, const float* dimg) {
+  return row_vec(C_e, dimg) == 0 && C_e >= 5 && (C_e <= 11 || tiles16 <= 8192);
+}
+
 int launch_jvp(const mer_plan* P, const mer_view* views, const float* v, const int32_t* tri, const int32_t* tri_id,
                const float* attr, const float* dattr, int C_a, int append_z, const float* img, int C_e,
                const float* dv, int flags, float* dimg, void* ws, hipStream_t st) {
@@ -341,9 +356,13 @@ int launch_jvp(const mer_plan* P, const mer_view* views, const float* v, const i
   if (base)
     hipLaunchKernelGGL(k_prep, dim3(1), dim3(1024), 0, st, views, P->n_views, 4, 4, tab, tab + (P->n_views + 1),
                        (long long*)nullptr);
-  if (P->total_btiles > 0)
-    hipLaunchKernelGGL(k_jvp, dim3((unsigned)P->total_btiles), dim3(256), 0, st, views, P->n_views, base, v, tri, tri_id,
-                       attr, dattr, C_a, append_z, img, C_e, dv, flags, dimg);
+#define MER_JVP(TS)                                                                                                    \
+  hipLaunchKernelGGL(k_jvp<TS>, dim3((unsigned)(P->total_btiles * (256 / (TS * TS)))), dim3(TS * TS), 0, st, views,    \
+                     P->n_views, base, v, tri, tri_id, attr, dattr, C_a, append_z, img, C_e, dv, flags, dimg)
+  if (P->total_btiles <= 0) return MER_OK;
+  if (small_jvp_tiles(P->total_btiles, C_e, dimg)) MER_JVP(8);
+  else MER_JVP(16);
+#undef MER_JVP
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }
 
