@@ -17,6 +17,7 @@ namespace mer {
 // often and the longer index costs more (16.8 and 18.3).  Each lane storing
 // its own row instead took 52 us for 11 channels (27 this way) and 101 for 17
 // (22): rows that are no multiple of 16 bytes.
+template <bool V4>
 __global__ void __launch_bounds__(256) k_interp(const mer_view* __restrict__ views, int n_views,
                                                 const float* __restrict__ attr, int C_a,
                                                 const float* __restrict__ v, const int32_t* __restrict__ tri,
@@ -81,8 +82,7 @@ __global__ void __launch_bounds__(256) k_interp(const mer_view* __restrict__ vie
       atomicOr(&s_gap, 1);
     }
   }
-  const bool v4 = C >= 12 && row_vec(C, out) == 4;
-  const int ld = v4 ? C | 1 : C;
+  const int ld = V4 ? C | 1 : C;
   float* so = s_out + threadIdx.x * ld;
   if (valid && idx[0] >= 0) {
     const float* a0 = attr + (vw.a_off + idx[0]) * C_a;
@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(256) k_interp(const mer_view* __restrict__ vie
   }
   const int n_here = (int)min((long long)blockDim.x, total_px - p0);
   float* dst = out + p0 * C;
-  if (v4) {
+  if constexpr (V4) {
     // the span's i-th four floats lie in row i / (C / 4); row and column move
     // on by the block's width without another division
     const int per = C >> 2, bs = (int)blockDim.x, dq = bs / per, dr = bs - dq * per;
@@ -128,9 +128,9 @@ __global__ void __launch_bounds__(256) k_interp(const mer_view* __restrict__ vie
         ++q;
       }
     }
-    return;
+  } else {
+    for (int i = threadIdx.x; i < n_here * C; i += blockDim.x) dst[i] = s_out[i];
   }
-  for (int i = threadIdx.x; i < n_here * C; i += blockDim.x) dst[i] = s_out[i];
 }
 
 // ------------------------------------------------------------- back faces
@@ -774,9 +774,14 @@ int launch_interpolate(const mer_plan* P, const mer_view* views, const float* at
   const long long n = P->total_px - P->px_begin;
   const int C = C_a + append_z;
   const int bs = C <= 32 ? 256 : 128;  // keeps the LDS staging buffer at or below 33 KB
-  const size_t lds = (size_t)bs * (C | 1) * sizeof(float);
-  hipLaunchKernelGGL(k_interp, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), lds, st, views, P->n_views, attr, C_a, v,
-                     tri, tri_id, bary, append_z, out, P->px_begin, P->total_px);
+  const bool v4 = C >= 12 && row_vec(C, out) == 4;  // of its own: 3 % slower for the others in one kernel
+  const size_t lds = (size_t)bs * (v4 ? C | 1 : C) * sizeof(float);
+#define MER_INTERP(V4)                                                                                                 \
+  hipLaunchKernelGGL(k_interp<V4>, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), lds, st, views, P->n_views, attr,    \
+                     C_a, v, tri, tri_id, bary, append_z, out, P->px_begin, P->total_px)
+  if (v4) MER_INTERP(true);
+  else MER_INTERP(false);
+#undef MER_INTERP
   return hipGetLastError() == hipSuccess ? MER_OK : MER_ELAUNCH;
 }
 
