@@ -52,16 +52,26 @@ struct CItem {
   CTile t;
   int part, parts, done, pad;
 };
+// Per tile: entries counted by rank (x), and by walking (y).
+struct Counts {
+  int2* p;
+  int shift;  // log2 of their distance, in counters
+  __device__ __forceinline__ int2& operator[](long long tile) const { return p[tile << shift]; }
+};
+
 static_assert(sizeof(CItem) == kItemBytes, "the plan's region of them");
 
 __global__ void __launch_bounds__(1024) k_cinit(const mer_view* __restrict__ views, int n_views, int ctl,
                                                 long long* __restrict__ tri_base, long long* __restrict__ tile_base,
-                                                long long* __restrict__ status, int2* __restrict__ count,
+                                                long long* __restrict__ status, const Counts count,
                                                 long long n_tiles, CItem* __restrict__ items, int n_items) {
-  for (int i = (int)(blockIdx.x * 1024 + threadIdx.x); i < n_items; i += (int)gridDim.x * 1024) items[i].t.xy = kGone;
-  for (long long i = (long long)blockIdx.x * 1024 + threadIdx.x; i < n_tiles; i += (long long)gridDim.x * 1024)
-    count[i] = make_int2(0, 0);
-  if (blockIdx.x == 0) view_prefix(views, n_views, ctl, ctl, tri_base, tile_base, status);
+  if (blockIdx.x > 0) {  // the first workgroup has the prefixes
+    const int step = (int)(gridDim.x - 1) * 1024, t = (int)(blockIdx.x - 1) * 1024 + (int)threadIdx.x;
+    for (int i = t; i < n_items; i += step) items[i].t.xy = kGone;
+    for (long long i = t; i < n_tiles; i += step) count[i] = make_int2(0, 0);
+    return;
+  }
+  view_prefix(views, n_views, ctl, ctl, tri_base, tile_base, status);
 }
 
 // ---------------------------------------------------------------- geometry
@@ -176,7 +186,7 @@ __global__ void __launch_bounds__(kBinBlock) k_ccount(const mer_view* __restrict
                                                       const float* __restrict__ v, const int32_t* __restrict__ tri,
                                                       const long long* __restrict__ tri_base,
                                                       const long long* __restrict__ tile_base, int total_tris, int ctl,
-                                                      int2* __restrict__ count, uint2* __restrict__ seg,
+                                                      const Counts count, uint2* __restrict__ seg,
                                                       int* __restrict__ seg_n, int* __restrict__ large,
                                                       long long* __restrict__ status) {
   __shared__ int s_key[kCSlots], s_cnt[kCSlots];
@@ -345,7 +355,7 @@ __global__ void __launch_bounds__(kBinBlock) k_clarge(const mer_view* __restrict
                                                       const long long* __restrict__ tri_base,
                                                       const long long* __restrict__ tile_base, int ctl,
                                                       const int* __restrict__ large, const long long* __restrict__ status,
-                                                      int2* __restrict__ count) {
+                                                      const Counts count) {
   walk_large(views, n_views, tri_base, tile_base, v, tri, ctl, large, (int)status[4], 0,
              [&](int, int ct) { atomicAdd(&count[ct].y, 1); });
 }
@@ -357,7 +367,7 @@ __global__ void __launch_bounds__(kBinBlock) k_clarge(const mer_view* __restrict
 // its parts (their number in status[3]), and its tile's keys are cleared.
 __global__ void __launch_bounds__(256) k_calloc(const mer_view* __restrict__ views, int n_views, int ctl,
                                                 const long long* __restrict__ tile_base, long long n_tiles,
-                                                int2* __restrict__ count, long long bin_cap,
+                                                const Counts count, long long bin_cap,
                                                 CTile* __restrict__ tiles, int item, int n_items,
                                                 CItem* __restrict__ items, unsigned long long* __restrict__ key,
                                                 long long* __restrict__ status) {
@@ -425,7 +435,7 @@ __global__ void __launch_bounds__(kBinBlock) k_cfill(const mer_view* __restrict_
                                                      const float* __restrict__ v, const int32_t* __restrict__ tri,
                                                      const long long* __restrict__ tri_base,
                                                      const long long* __restrict__ tile_base, int ctl, int n_groups,
-                                                     int2* __restrict__ count, const uint2* __restrict__ seg,
+                                                     const Counts count, const uint2* __restrict__ seg,
                                                      const int* __restrict__ seg_n, const int* __restrict__ large,
                                                      const long long* __restrict__ status,
                                                      const CTile* __restrict__ tiles, int* __restrict__ bins) {
@@ -506,7 +516,7 @@ constexpr int kMaskGen = 16;  // bit of the candidate's tile mask: general recor
 // STAGED: the resolve writes its image rows by way of LDS (below).
 template <int CTL, int NT, bool STAGED>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_craster(const mer_view* __restrict__ views, const CTile* __restrict__ tiles,
-                                                 const int2* __restrict__ count, const int* __restrict__ bins,
+                                                 const Counts count, const int* __restrict__ bins,
                                                  const long long* __restrict__ tri_base, int direct, ResolveOut R,
                                                  int split0, int n_split, int n_tiles, CItem* __restrict__ items,
                                                  unsigned long long* __restrict__ key,
@@ -535,8 +545,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) k_
     T.xy = ((unsigned)g - q * tiles_x) | q << 16;
   } else {
     T = *(split ? &items[sb].t : tiles + g);
-    // integrity: the fill pass takes every walked count back to 0
-    if (!split && tid == 0 && count[g].y != 0) atomicAdd((unsigned long long*)status + 6, 1ull);
+    // integrity: the fill pass takes every walked count back to 0; every
+    // 256th tile's workgroup looks at as many
+    if (!split && (g & (NT - 1)) == 0 && g + tid < n_tiles && count[g + tid].y != 0)
+      atomicAdd((unsigned long long*)status + 6, 1ull);
     if (T.xy & kGone) return;
   }
   const mer_view vw = views[T.view];
@@ -987,7 +999,7 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
   long long* tile_base = tri_base + (P->n_views + 1);
   long long* status = (long long*)(w + P->off_status);
   const CoarsePlan cp = coarse_plan(P);
-  int2* count = (int2*)(w + cp.off_count);
+  const Counts count = {(int2*)(w + cp.off_count), cp.count_shift};
   CTile* tiles = (CTile*)(w + cp.off_tile);
   uint2* seg = (uint2*)(w + P->off_rec);
   int* bins = (int*)(w + P->off_bins);
@@ -999,7 +1011,7 @@ static int launch_coarse(const mer_plan* P, const mer_view* views, const Resolve
   const long long nt = cp.n;
   const int direct = direct_tiles(P, nt);
   if (!direct) {
-    hipLaunchKernelGGL(k_cinit, dim3((unsigned)min((nt + 1023) / 1024, 512ll)), dim3(1024), 0, st, views, P->n_views,
+    hipLaunchKernelGGL(k_cinit, dim3(1 + (unsigned)min((nt + 1023) / 1024, 512ll)), dim3(1024), 0, st, views, P->n_views,
                        ctl, tri_base, tile_base, status, count, nt, items, (int)cp.n_items);
     if (P->total_tris > 0) {
       hipLaunchKernelGGL(k_ccount, dim3((unsigned)P->n_bingroups), dim3(kBinBlock), 0, st, views, P->n_views, R.v, R.tri,
