@@ -73,8 +73,8 @@ typedef struct mer_view {
 /* How triangles are binned.  By default (small_px >= 0) each triangle is
  * listed in the coarse screen tiles it may cover, 8, 16 or 32 pixels square
  * (mer_plan_init picks the side from the view sizes and the triangle count),
- * and the tile's workgroup sorts them into 8x8 pixels itself; tile_w, tile_h
- * and big_tiles have no effect.  With small_px < 0 every triangle is listed in
+ * and the tile's workgroup sorts them into 8x8 pixels itself; tile_w, tile_h,
+ * big_tiles and the value of small_px have no effect.  With small_px < 0 every triangle is listed in
  * the tile_w x tile_h tiles it may cover and the rasterizer takes one such
  * tile per workgroup.  bin_cap is the capacity of the list pool (entries, at
  * most INT_MAX - 1; 0 picks a default from the triangle and tile counts);
@@ -99,7 +99,7 @@ typedef struct mer_plan {
   int64_t n_part;
   int64_t total_btiles, off_bviewtab; /* 16x16 tiles of the backward sweep */
   int64_t total_v, off_vbase;         /* screen vertices over all views, their per-view prefix */
-  int64_t off_bloss;                  /* per-wave partial sums of the fused L2 loss */
+  int64_t off_bloss;                  /* partial sums of the fused L2 loss, one per 16x16 tile (room for four) */
   int64_t off_big, off_bign;          /* per-workgroup lists of large triangles, lengths + offsets */
   int64_t big_tiles;                  /* small_px <= 0: see mer_tuning; else the coarse tiles:
                                          their number << 8 | log2 of their side */
@@ -256,7 +256,7 @@ int mer_backward_fused(const mer_plan *plan, const mer_view *views_dev, const fl
  * rendered images): dL/d(img) = 2 w (img - target) is formed inside the
  * sweep instead of being read from memory, and when `loss` (one device
  * float, accumulated) is not NULL, L over every pixel of every view is added
- * to it (partial sums per wave of pixels, then one atomic).  target: float
+ * to it (partial sums per 16x16 tile, then one atomic).  target: float
  * [total_px, C_e], the same layout as img.  Other arguments as
  * mer_backward_fused. */
 int mer_backward_l2(const mer_plan *plan, const mer_view *views_dev, const float *v, const int32_t *tri,
@@ -268,8 +268,8 @@ int mer_backward_l2(const mer_plan *plan, const mer_view *views_dev, const float
  * one (code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation).  Same arguments and results as mer_backward_l2 minus
  * `ws`; the small scratch the backward needs (the per-view tile prefix,
- * 2 (n_views + 1) int64, and, when `loss` is not NULL, one float per wave of
- * 64 pixels) lives in a fixed array of MER_NOALLOC_SCRATCH_BYTES bytes in
+ * 2 (n_views + 1) int64, and, when `loss` is not NULL, room for four floats
+ * per 16x16 tile) lives in a fixed array of MER_NOALLOC_SCRATCH_BYTES bytes in
  * the library's device memory, one per GPU, kept until the process ends.
  * The call allocates nothing: it uses the current device's array (the
  * stream must belong to the current device), whose address is looked up on

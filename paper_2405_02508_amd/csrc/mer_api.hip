@@ -19,11 +19,11 @@ using mer::align256;
 // where 16 x 16 gives fewer than 16 workgroups a compute unit and the lists
 // are long (a tile runs as long as its list, and the entries that triangles
 // over several small tiles add are few beside it).
-// Steps measured on both sides of the lines (us a pass, 32 / 16 pixels): 1196
-// tiles of 214 triangles 535 / 490, 1452 of 74 119 / 131, 1444 of 2 102 / 114,
-// 625 of 131 111 / 86; (16 / 8 pixels) 64 tiles of 16 x 16 with 3125
-// triangles each 90 / 69, 2688 with 583 174 / 144, 25 with 39 38 / 53, 2500
-// with 33 82 / 113.
+// Measured on both sides of the lines (rasterize and interpolate, us, 32 / 16
+// pixels): 1190 tiles of 214 triangles 134 / 96, 1444 of 74 71 / 71, 1444 of 2
+// 59 / 66, 625 of 131 76 / 54, 2116 of 30 76 / 98; (16 / 8 pixels) 64 tiles of
+// 16 x 16 with 3125 triangles each 58 / 37, 2688 with 583 83 / 78, 900 with 300
+// 92 / 72, 8450 with 150 251 / 410, 2500 with 33 55 / 99.
 int coarse_log2(int64_t tiles32, int64_t tiles16, int64_t tris) {
   if (tiles32 >= 2048 || (tiles32 >= 1024 && tris <= 128 * tiles32)) return 5;
   return tiles16 < 4096 && tris >= 256 * tiles16 ? 3 : 4;
@@ -111,7 +111,7 @@ int mer_plan_init(const mer_view* views, int n_views, const mer_tuning* tun, mer
   P->off_vbase = off;
   off = align256(off + (int64_t)(n_views + 1) * 8);
   P->off_bloss = off;
-  off = align256(off + btiles * 4 * 4);  // one float per wave
+  off = align256(off + btiles * 4 * 4);  // one float per tile is written; four were, and the layout stays
   const int64_t bin_groups = (tris + mer::kBinBlock - 1) / mer::kBinBlock;
   P->off_big = off;
   off = align256(off + bin_groups * mer::kBinBlock * 4);
@@ -321,7 +321,8 @@ int mer_backward_l2_noalloc(const mer_plan* P, const mer_view* views_dev, const 
   if (!std::isfinite(weight)) return MER_EINVAL;
   if (!(flags & MER_SKIP_EDGE) && !g_v) return MER_EINVAL;
   if (!(flags & MER_SKIP_INTERP) && (!attr || C_a < 1 || C_a > 64 || C > C_e)) return MER_EINVAL;
-  // the scratch holds the per-view tile prefix, then the per-wave loss partials
+  // the scratch holds the per-view tile prefix, then the loss partials: four
+  // floats a tile as ever (one is written), so that the same plans are refused
   const int64_t tab_bytes = align256(2 * (int64_t)(P->n_views + 1) * 8);
   const int64_t need = tab_bytes + (loss ? 4 * P->total_btiles * (int64_t)sizeof(float) : 0);
   if (need > (int64_t)kScratchBytes) return MER_ESCRATCH;

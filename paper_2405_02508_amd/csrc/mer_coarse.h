@@ -20,7 +20,7 @@
 // triangle is snapped and prepared once per coarse tile.  Measured, rasterize
 // and interpolate, before and after (us): 16 views of the 2M-triangle pair
 // 11,700 and 5,950 (k_craster 4,700: vector issue 65 % of it, the rest LDS
-// latency and barriers; count 860, fill 380); 256 scenes 2,750 and 1,980
+// latency and barriers; count 740, fill 400); 256 scenes 2,750 and 1,980
 // (1,700 + 180 + 95); 64 head views 1,470 and 680 (570 + 70 + 24; its writes
 // alone take 440 at the rate of a large copy); one 64 x 64 view 41 and 12.
 // The visible triangle is the largest (1/z, ~id) key at every pixel, in any
