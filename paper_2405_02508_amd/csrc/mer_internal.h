@@ -9,12 +9,13 @@ constexpr int kBinBlock = 256;  // threads per workgroup of the binning passes (
 
 constexpr int kLongList = 4096;  // entries of a coarse tile that one workgroup takes: sixteen rounds, about 40 us
 constexpr int kItemBytes = 32;
-// Plans of at most this many coarse tiles keep each tile's counters on a cache
-// line of their own: the adds of triangles in no order, one for each, went to
-// one line for 16 tiles.  300,000 triangles of 4 px over 256 tiles 151 us, 59
-// padded, 1,500,000 over 4096 tiles 250 and 216; 16 views of 10,752 tiles take
-// 3 us longer to clear and read padded ones.
-constexpr int kPaddedTiles = 4096;
+// Plans of at most so many coarse tiles, with so many triangles for each, keep
+// each tile's counters on a cache line of their own: the adds of triangles in
+// no order, one for each, went to one line for 16 tiles.  300,000 triangles of 4
+// px over 256 tiles 151 us, 59 padded, 1,500,000 over 4096 tiles 250 and 216.
+// Clearing and reading padded ones takes 3 us longer for 10,752 tiles, and 1 us
+// for 1024 (of 160 triangles).
+constexpr int kPaddedTiles = 4096, kPaddedTris = 192;
 
 // The coarse tiles of a plan (small_px > 0) and their regions of the
 // workspace, after the last one mer_plan names: mer_plan lies in the caller's
@@ -34,7 +35,7 @@ inline CoarsePlan coarse_plan(const mer_plan* P) {
   c.ctl = (int)(P->big_tiles & 255);
   c.n = P->big_tiles >> 8;
   c.off_count = align256(P->off_bigflat + P->total_tris * 4);
-  c.count_shift = c.n <= kPaddedTiles ? 4 : 0;
+  c.count_shift = c.n <= kPaddedTiles && P->total_tris >= kPaddedTris * c.n ? 4 : 0;
   c.off_tile = align256(c.off_count + (c.n * 8 << c.count_shift));
   c.off_item = align256(c.off_tile + c.n * 16);
   // Lists longer than kLongList and than two parts are split (mer_coarse.h).

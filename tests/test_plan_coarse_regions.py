@@ -39,7 +39,8 @@ VIEWS = {
     "one_px": lambda: _one(1, 1, 0), "no_triangles": lambda: _one(640, 480, 0), "short": lambda: _one(300, 200, 4096),
     "first_parts": lambda: _one(300, 200, 4097), "fine": lambda: _one(500, 300, 200000),
     "millions": lambda: _one(2048, 2048, 2097152), "more": lambda: _one(2048, 2048, 2097153),
-    "padded": lambda: _one(2048, 2048, 5000), "packed": lambda: _one(2048, 2049, 5000),
+    "padded": lambda: _one(2048, 2048, 786432), "sparse": lambda: _one(2048, 2048, 786431),
+    "packed": lambda: _one(2048, 2049, 900000),
     "head": lambda: _full_views(3), "pair": lambda: _full_views(4), "batch": lambda: _full_views(5),
 }
 
@@ -56,7 +57,8 @@ def test_coarse_regions_hold_what_the_kernels_index(name, tile):
     assert off == P.off_bigflat
     item, n = parts(int(P.total_tris))
     assert n <= 4096 + 8 and (n == 0 or n * item > 2 * P.total_tris - item)
-    line = 128 // COUNT_BYTES if P.total_ctiles <= 4096 else 1  # few tiles' counters have a line each
+    # few tiles' counters have a line each, where there are many triangles for each
+    line = 128 // COUNT_BYTES if P.total_ctiles <= 4096 and P.total_tris >= 192 * P.total_ctiles else 1
     for more in (P.total_ctiles * COUNT_BYTES * line, P.total_ctiles * TILE_BYTES, n * ITEM_BYTES):
         off, size = align256(off + size), more
     assert P.ws_bytes == align256(off + size)
