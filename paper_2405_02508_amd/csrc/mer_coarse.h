@@ -19,7 +19,7 @@
 // but 1.9 of 32 x 32, so the lists hold less than half the entries, and a
 // triangle is snapped and prepared once per coarse tile.  Measured, rasterize
 // and interpolate, before and after (us): 16 views of the 2M-triangle pair
-// 11,700 and 5,950 (k_craster 4,700: vector issue 65 % of it, the rest LDS
+// 11,700 and 5,950 (k_craster 4,600: vector issue 71 % of it, the rest LDS
 // latency and barriers; count 740, fill 400); 256 scenes 2,750 and 1,980
 // (1,700 + 180 + 95); 64 head views 1,470 and 680 (570 + 70 + 24; its writes
 // alone take 440 at the rate of a large copy); one 64 x 64 view 41 and 12.
